@@ -18,6 +18,8 @@
 //                 Hermitian sum (1/m)(P_0 + P_{m/2} + 2 Re sum_{0<j<m/2} P_j)
 //                 gives the estimate.
 //   sample_stats: FP64 mean and unbiased variance over samples per network.
+#include <algorithm>
+
 #include "m1_device.h"
 
 #include <hip/hip_bf16.h>
@@ -28,97 +30,578 @@ namespace {
 using namespace m1dev;
 
 
-constexpr int kStageMaxLog2M = 12;  // largest log2 m that stages the column hash words
+// Four consecutive entries of a row, loaded with one or two vector loads from
+// any element-aligned address.
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x4e __attribute__((ext_vector_type(4), aligned(8)));
+typedef unsigned short u16x4e __attribute__((ext_vector_type(4), aligned(2)));
+template <typename T>
+struct Quad;
+template <>
+struct Quad<float> {
+  using type = f32x4e;
+};
+template <>
+struct Quad<double> {
+  using type = f64x4e;
+};
+template <>
+struct Quad<uint16_t> {
+  using type = u16x4e;
+};
 
-// Waves per SIMD the register allocation must allow: four (two blocks per CU)
-// for the 512-thread FP32 blocks whose loop keeps 8 loads in flight (their
-// LDS leaves room for two blocks at m = 1024); no constraint otherwise.
-template <typename T, int SB, int NT>
-constexpr int kScatterWavesPerEU = (NT == 512 && sizeof(T) == 4 && SB * 4 <= 16) ? 4 : 1;
+// x with its sign flipped when bit (kSignBit or 0) is set.
+__device__ __forceinline__ float flip_sign(float x, uint32_t bit) { return __uint_as_float(__float_as_uint(x) ^ bit); }
+__device__ __forceinline__ double flip_sign(double x, uint32_t bit) {
+  return __hiloint2double((int)((uint32_t)__double2hiint(x) ^ bit), __double2loint(x));
+}
 
-// One block streams one slot and accumulates the sketches of SB samples (see
-// scatter_slot), then writes them out as floating point.
-// Blocks of 256 threads with one bank, 512 with two (twice the accumulator LDS
-// per block, the same waves per CU); NT = 1024 when one block fills a CU's LDS
-// (large m or many samples per pass), so that the CU still runs 16 waves.
-// RANGED (m above kMaxLog2Acc buckets): blockIdx.z selects the range of
-// 2^log2acc buckets the block accumulates (one bank, one sample per pass).
-// Fixed-point scale: with bound_in, slot b's entries are all below
-// bound_in[b] (a power of two, or 0 for an all-zero slot) and the scale is set
-// once; otherwise the block keeps a running maximum (a barrier per load round)
-// and, with bound_out, records the power-of-two bound it ends with.
-// Sample batch blockIdx.y + y0 of the launch's samples.
-template <typename T, typename A, int SB, int BANKS, bool RANGED = false, int NT = 256 * BANKS>
-__global__ __launch_bounds__(NT, (kScatterWavesPerEU<T, SB, NT>)) void m1_scatter_kernel(
-    const ScatterSlot *__restrict__ slots, const ModeDesc *__restrict__ modes,
-    const void *const *__restrict__ data, const int32_t *__restrict__ tables, int64_t W,
-    int64_t samples, int log2m, int log2acc, int64_t n_slots, A *__restrict__ ybuf,
-    const double *__restrict__ bound_in, double *__restrict__ bound_out, int y0) {
-  // No static LDS: the accumulators start at LDS address 0, so their offsets
-  // need no base add per term.
+// The packed row words of SB samples (one 16-byte LDS read per four).
+template <int SB>
+__device__ __forceinline__ void load_row(const uint32_t *p, uint32_t *out) {
+  if constexpr (SB == 1)
+    out[0] = p[0];
+  else
+    load_cols<SB>(p, out);
+}
+
+// One block streams one slot and accumulates the sketches of SB samples at a
+// time in LDS in 64-bit fixed point, then writes them out as floating point,
+// for the sample batches [grp gs, grp gs + gs) of the launch.
+//
+// Columns stay with their threads: thread t takes the four columns 4 (t mod V)
+// .. + 3 (V = ceil(L / 4) vectors per row; the last vector of a row of other
+// length starts at L - 4 and its columns already covered are scaled by 0) of
+// the rows t / V + k (NT / V).  Its SB x 4 column words are held in registers
+// for a batch, no term divides or tests a row end, and a vector reads only its
+// row's SB words from LDS (rowt, one 16-byte broadcast read for four samples),
+// a chunk of kRowChunk rows at a time.
+// A term is then one add, one and-or and the LDS atomic with BANKS = 2:
+// sketches are pairs of banks of m words, +1 terms in the positive bank, -1
+// terms in the negative one, the sketch their difference.  Sample s's positive
+// bank is at byte 8 m s, its negative bank signbit further (a power of two of
+// at least 16 m); the words hold bucket * 8 plus signbit for sign -1, so the
+// sum of a row and a column word carries the product of the signs in the
+// signbit position (the bucket sum stays below 16 m).  With BANKS = 1 (half the
+// LDS) the signs are in bit 31 and the product flips the sign of the entry
+// before its conversion.
+// What bounds it: random 64-bit LDS atomics.  16 lanes at a time fall into the
+// 32 pairs of LDS banks, 2.35 deep on average: 9.4 cycles per wave instruction,
+// 5.5 of them conflicts (LDS counters), against three vector instructions
+// at four samples and two banks.
+//
+// The hash words of a batch (all modes of the slot's tensor, complement
+// applied, [word][sample]) are staged in LDS for tensors of at most four modes
+// of together at most kStageWords indices; the next batch's are loaded during
+// the current one.  Other tensors read the global tables.  Everything else a
+// block needs is set up once for all of its batches: measured on the batch of
+// 4096 networks, a block's start (its chain of dependent loads) takes 8 to 9
+// us, as long as the scatter itself when each block takes one batch.
+//
+// The fixed-point scale is 62 - lgN - e for |x| < 2^e and N <= 2^lgN terms, so
+// sums cannot overflow and do not depend on the order of the atomics.  bound_in:
+// per slot the power of two 2^e (0 for an all-zero slot) recorded before;
+// without it the block first takes the maximum over its slot (read again by
+// the scatter, from the caches); the first group's blocks record it in
+// bound_out.
+//
+// RANGED (m above 2^kMaxLog2Acc buckets, one bank, one sample): the block takes
+// the ranges of 2^kMaxLog2Acc buckets one after the other and drops the terms
+// outside the current one.
+//
+// slots: in decreasing order of size (pad: the slot's number), so that the last
+// blocks to start are short.  The groups of the same 8 slots are neighbours:
+// block b runs on XCD b mod 8, so a slot's groups share an L2.
+// Registers: six waves per SIMD (three blocks per CU) for 512-thread blocks with
+// one bank, whose LDS leaves room for them at m = 1024 (batch of 4096 networks:
+// 2.64 against 2.75 ms per call with four, and with four row vectors in flight
+// instead of two), four otherwise.
+template <typename T, typename A, int SB, int BANKS, int NT, bool RANGED = false>
+__global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16 ? 6 : 4) void m1_scatter_kernel(
+    const ScatterSlot *__restrict__ slots, int32_t n, const ModeDesc *__restrict__ modes,
+    const void *const *__restrict__ data, const int32_t *__restrict__ tables, int64_t W, int64_t samples,
+    int log2m, int64_t n_slots, A *__restrict__ ybuf, const double *__restrict__ bound_in,
+    double *__restrict__ bound_out, int32_t gs, int32_t groups, int32_t gx) {
+  static_assert(!RANGED || (BANKS == 1 && SB == 1), "bucket ranges use one bank and one sample");
+  using Q = typename Quad<T>::type;
+  constexpr int U = BANKS == 1 || SB * sizeof(T) >= 32 ? 2 : 4;  // row vectors in flight per thread
+  static_assert(kStageWords <= NT, "one staged word per thread");
+  // No static LDS: the accumulators start at LDS address 0.
   extern __shared__ __align__(16) unsigned char smem[];
-  const ScatterSlot sl = slots[blockIdx.x];
+  const uint32_t blk = blockIdx.x / (8u * (uint32_t)gx), rem = blockIdx.x - blk * 8u * (uint32_t)gx;
+  const int32_t pos = (int32_t)(blk * 8u + (rem & 7u));
+  const int32_t grp = (int32_t)(rem >> 3) + (int32_t)blockIdx.y * gx;
+  if (pos >= n || grp >= groups) return;  // padding of the grid
+  const ScatterSlot sl = slots[pos];
+  const int32_t sid = sl.pad;
   const int tid = threadIdx.x;
-  const int64_t s0 = ((int64_t)blockIdx.y + y0) * SB;
-  const int nsb = (int)min((int64_t)SB, samples - s0);
-  const uint32_t m = 1u << log2m;
-  const uint32_t ma = RANGED ? 1u << log2acc : m, amask = ma - 1;  // accumulator words per sample
-  const uint32_t r0 = RANGED ? blockIdx.z * ma : 0u;              // first bucket of the range
-  // BANKS banks of m words per sample (see scatter_slot), then the tables
-  const uint32_t signbit = BANKS == 2 ? sign_bank_offset(SB, m) : 0u;
-  const size_t acc_bytes = BANKS == 2 ? sign_bank_bytes(SB, m) : (size_t)SB * 8 * ma;
-  const size_t acc_end = (acc_bytes + 15) & ~(size_t)15;
+  const uint32_t m = 1u << log2m, mask = m - 1;
+  constexpr int log2acc = kMaxLog2Acc;
+  const uint32_t ma = RANGED ? 1u << log2acc : m;  // accumulator words per sample
+  const uint32_t signbit = BANKS == 2 ? sign_bank_offset(SB, m) : kSignBit;
+  const uint32_t acc_bytes = BANKS == 2 ? (uint32_t)sign_bank_bytes(SB, m) : (uint32_t)SB * 8u * ma;
+  const uint32_t acc_end = (acc_bytes + 15u) & ~15u;
   unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem);
-  unsigned long long *s_max = reinterpret_cast<unsigned long long *>(smem + acc_end);  // [2]
-  uint32_t *tabs = reinterpret_cast<uint32_t *>(smem + acc_end + 16);  // column and row tables
-  // Up to m = 4096 the column tables are built from hash words staged in the
-  // not yet cleared accumulators (scatter_slot clears them afterwards); above
-  // it the clear of the large accumulators is better done first (measured).
-  const bool stage = log2m <= kStageMaxLog2M;
-  if (!stage) lds_zero(acc, (uint32_t)acc_bytes, tid, NT);
-  if (tid < 2) s_max[tid] = 0ull;
-  const uint32_t N = (uint32_t)sl.rows * (uint32_t)sl.L;
-  FixedScale fs;
-  fs.lgN = max(N > 1 ? 32 - __clz(N - 1) : 0, 11);
-  if (bound_in != nullptr) {
-    const double b = bound_in[blockIdx.x];
-    if (b > 0.0) {
-      int e;
-      (void)frexp(b, &e);  // b = 2^(e - 1)
-      fs.scale = 62 - fs.lgN - (e - 1);
-      fs.sc = ldexp(1.0, fs.scale);
-      fs.bound = b;
-    }
-    fs.known = true;
-  }
-  scatter_slot<T, SB, BANKS, NT, RANGED>(sl, modes, data, tables + s0 * W, W, nsb, log2m, acc, 8u * ma, signbit,
-                                         tabs, s_max, fs, blockIdx.z, RANGED ? log2acc : -1,
-                                         stage ? reinterpret_cast<uint32_t *>(acc) : nullptr,
-                                         stage ? (uint32_t)(acc_bytes / 4) : 0u);
-  if (bound_out != nullptr && tid == 0 && blockIdx.y == 0 && blockIdx.z == 0) bound_out[blockIdx.x] = fs.bound;
-  const unsigned long long *neg = acc + signbit / 8;
-  const int lga = RANGED ? log2acc : log2m;
-  // (positive bank minus negative bank) 2^-scale, four buckets per thread and
-  // 16-byte accesses when a sketch has at least four
-  auto value = [&](int i) {
-    const long long v = BANKS == 2 ? (long long)(acc[i] - neg[i]) : (long long)acc[i];
-    return (A)ldexp((double)v, -fs.scale);
+  uint32_t *rowt = reinterpret_cast<uint32_t *>(smem + acc_end);  // [kRowChunk][SB]
+  uint32_t *stage = rowt + kRowChunk * SB;                        // [kStageWords][SB]
+  unsigned long long *s_max = reinterpret_cast<unsigned long long *>(stage + kStageWords * SB);
+  const int L = sl.L, rows = sl.rows;
+  const T __attribute__((address_space(1))) *X =
+      (const T __attribute__((address_space(1))) *)(reinterpret_cast<const T *>(data[sl.tensor]) +
+                                                    sl.row0 * (int64_t)L);
+
+  // The thread's columns and first row; threads past the last whole row of
+  // vectors have no work in the loop.
+  const int V = (L + 3) >> 2, RP = NT / V;  // L <= 1024 <= 4 NT
+  const int rt = tid / V, v = tid - rt * V;
+  const bool active = rt < RP;
+  const int c0 = max(0, min(4 * v, L - 4));
+  auto load = [&](int r) {
+    const int off = min(r, rows - 1) * L + c0;
+    if (L >= 4) return *(const Q __attribute__((address_space(1))) *)(X + off);
+    Q q = {};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (i < L) q[i] = X[off + i];
+    return q;
   };
-  if (lga >= 2) {
-    for (int i4 = tid; i4 < (nsb << (lga - 2)); i4 += NT) {
-      const int i = 4 * i4, s = i >> lga, b = i & (int)amask;
-      const A v0 = value(i), v1 = value(i + 1), v2 = value(i + 2), v3 = value(i + 3);
-      A *dst = ybuf + ((s0 + s) * n_slots + blockIdx.x) * (int64_t)m + r0 + b;
-      if constexpr (sizeof(A) == 4) {
-        *reinterpret_cast<float4 *>(dst) = make_float4(v0, v1, v2, v3);
-      } else {
-        reinterpret_cast<double2 *>(dst)[0] = make_double2(v0, v1);
-        reinterpret_cast<double2 *>(dst)[1] = make_double2(v2, v3);
+  Q nxt[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) nxt[u] = load(rt + u * RP);
+
+  // The tensor's modes, first ones first; the staged words of mode j start at
+  // word mo[j] (mode sizes past the last are 0).
+  const int q = sl.q, split = sl.split, mode0 = sl.mode0;
+  int mn[4], mo[4], tot = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    mn[j] = j < q ? modes[mode0 + j].n : 0;
+    mo[j] = tot;
+    tot += mn[j];
+  }
+  const bool staged = q <= 4 && tot <= kStageWords;  // uniform
+  // This thread's staged word: its table offset and complement flag.
+  int64_t w_off = 0;
+  bool w_comp = false;
+  if (staged && tid < tot) {
+    const int j = tid >= mo[3] && mn[3] > 0 ? 3 : tid >= mo[2] && mn[2] > 0 ? 2 : tid >= mo[1] && mn[1] > 0 ? 1 : 0;
+    const ModeDesc md = modes[mode0 + j];
+    const int base = j == 0 ? 0 : j == 1 ? mo[1] : j == 2 ? mo[2] : mo[3];
+    w_off = md.table_off + (tid - base);
+    w_comp = md.comp != 0;
+  }
+  const int32_t batch_end = min((grp + 1) * gs, (int32_t)((samples + SB - 1) / SB));
+  uint32_t pre[SB];  // the next batch's staged words
+  auto fetch = [&](int32_t b) {
+    if (staged && tid < tot && b < batch_end) {
+#pragma unroll
+      for (int s = 0; s < SB; ++s)
+        pre[s] = (uint32_t)tables[min((int64_t)b * SB + s, samples - 1) * W + w_off];
+    }
+  };
+  auto put = [&](int32_t b) {
+    if (staged && tid < tot && b < batch_end) {
+#pragma unroll
+      for (int s = 0; s < SB; ++s) {
+        uint32_t h = pre[s] & ~kSignBit;
+        if (w_comp) h = (m - h) & mask;
+        stage[tid * SB + s] = (h << 3) | (pre[s] & kSignBit);
       }
     }
+  };
+  fetch(grp * gs);
+
+  // Largest |x| of the slot, when it was not recorded before.
+  double bound;
+  if (bound_in != nullptr) {
+    bound = bound_in[sid];
   } else {
-    for (int i = tid; i < (nsb << lga); i += NT)
-      ybuf[((s0 + (i >> lga)) * n_slots + blockIdx.x) * (int64_t)m + r0 + (i & (int)amask)] = value(i);
+    const uint32_t N = (uint32_t)rows * (uint32_t)L;
+    double lmax = 0.0;
+    if (tid == 0) s_max[0] = 0ull;
+    if (RP * U >= rows) {  // all of it is in nxt
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lmax = fmax(lmax, fabs((double)to_acc_any((T)nxt[u][i])));
+    } else {
+      const Q __attribute__((address_space(1))) *Xq = (const Q __attribute__((address_space(1))) *)X;
+      const uint32_t NQ = N / 4;
+      for (uint32_t i0 = tid; i0 < NQ; i0 += NT * U) {
+        Q t[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) t[u] = Xq[min(i0 + (uint32_t)u * NT, NQ - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) lmax = fmax(lmax, fabs((double)to_acc_any((T)t[u][i])));
+      }
+      if (4 * NQ + tid < N) lmax = fmax(lmax, fabs((double)to_acc_any((T)X[4 * NQ + tid])));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lmax = fmax(lmax, __shfl_xor(lmax, off, 64));
+    __syncthreads();
+    if ((tid & 63) == 0) atomicMax(s_max, (unsigned long long)__double_as_longlong(lmax));
+    __syncthreads();
+    const double bm = __longlong_as_double((long long)s_max[0]);
+    int e = 0;
+    (void)frexp(bm, &e);  // bm < 2^e
+    bound = bm > 0.0 ? ldexp(1.0, e) : 0.0;
+    if (bound_out != nullptr && tid == 0 && grp == 0) bound_out[sid] = bound;
+  }
+  int scale = 0;
+  if (bound > 0.0) {
+    const uint32_t N = (uint32_t)rows * (uint32_t)L;
+    int e;
+    (void)frexp(bound, &e);  // bound = 2^(e - 1)
+    scale = 62 - max(N > 1 ? 32 - __clz(N - 1) : 0, 11) - (e - 1);
+  }
+  const double sc = ldexp(1.0, scale);
+  double scq[4];  // 0 for columns past the row or covered by the vector before
+#pragma unroll
+  for (int i = 0; i < 4; ++i) scq[i] = (c0 + i >= 4 * v && i < L) ? sc : 0.0;
+
+  // Byte address of a term: ((row word + column word) & amask) | soff[s], one
+  // and-or instruction.  The values pass through empty asm statements so that
+  // the mask is held in a vector register (the instruction takes one scalar
+  // operand) and the LDS base, 0 here (the block has no static LDS), is not
+  // added again for every term.
+  uint32_t amask = (mask << 3) | (BANKS == 2 ? signbit : 0u);
+  asm("" : "+v"(amask));
+  uint32_t soff[SB];
+#pragma unroll
+  for (int s = 0; s < SB; ++s) {
+    soff[s] = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char *)smem) +
+              (uint32_t)s * 8u * ma;
+    asm("" : "+s"(soff[s]));
+  }
+  auto add = [](uint32_t byte, long long t) {
+    __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long *)byte, (unsigned long long)t,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  // A sum of words (bucket * 8, sign in bit 31) as the address part of a term.
+  auto to_offset = [&](uint32_t w) {
+    return (w & (mask << 3)) | ((uint32_t)((int32_t)w >> 31) & signbit);
+  };
+  constexpr double kMagic = 6755399441055744.0;  // 1.5 2^52: x sc + kMagic holds round(x sc) in its low bits
+  const long long kMagicBits = __double_as_longlong(kMagic);
+  // idx / n for idx < 2^21: (idx + 1/2) / n is at least 1 / 2n from an integer
+  auto divide = [](uint32_t idx, float rn) { return (uint32_t)(((float)idx + 0.5f) * rn); };
+  const float rn[4] = {1.0f / (float)max(mn[0], 1), 1.0f / (float)max(mn[1], 1), 1.0f / (float)max(mn[2], 1),
+                       1.0f / (float)max(mn[3], 1)};
+  // Sum over the modes [j0, j1) of the words of index idx, for the SB samples
+  // of the batch starting at s0.
+  auto words = [&](uint32_t idx, int j0, int j1, int64_t s0, uint32_t *w) {
+#pragma unroll
+    for (int s = 0; s < SB; ++s) w[s] = 0;
+    if (staged) {
+#pragma unroll
+      for (int j = 3; j >= 0; --j) {
+        if (j < j0 || j >= j1) continue;
+        const uint32_t qt = j > j0 ? divide(idx, rn[j]) : 0u;
+        uint32_t t[SB];
+        load_row<SB>(stage + (mo[j] + (int)(idx - qt * (uint32_t)mn[j])) * SB, t);
+        idx = qt;
+#pragma unroll
+        for (int s = 0; s < SB; ++s) w[s] += t[s];
+      }
+    } else {
+      for (int j = j1 - 1; j >= j0; --j) {
+        const ModeDesc md = modes[mode0 + j];
+        const uint32_t qt = j > j0 ? idx / (uint32_t)md.n : 0u;
+        const uint32_t d = idx - qt * (uint32_t)md.n;
+        idx = qt;
+#pragma unroll
+        for (int s = 0; s < SB; ++s) {
+          const uint32_t t = (uint32_t)tables[min(s0 + s, samples - 1) * W + md.table_off + d];
+          uint32_t h = t & ~kSignBit;
+          if (md.comp) h = (m - h) & mask;
+          // (the sum is reduced each time: the bucket part stays clear of bit 31 for any order)
+          w[s] = ((w[s] + (h << 3)) & (mask << 3)) | ((w[s] ^ t) & kSignBit);
+        }
+      }
+    }
+  };
+
+  lds_zero(acc, acc_bytes, tid, NT);
+  put(grp * gs);
+  for (int32_t batch = grp * gs; batch < batch_end; ++batch) {
+    const int64_t s0 = (int64_t)batch * SB;
+    __syncthreads();  // the staged words are there, the accumulators cleared
+    uint32_t lv[SB][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t w[SB];
+      words((uint32_t)min(c0 + i, L - 1), split, q, s0, w);
+#pragma unroll
+      for (int s = 0; s < SB; ++s) lv[s][i] = to_offset(w[s]);
+    }
+    fetch(batch + 1);
+    const int nranges = RANGED ? 1 << (log2m - log2acc) : 1;
+    for (int range = 0; range < nranges; ++range) {
+      const uint32_t rlo = (uint32_t)range << (3 + log2acc), rlen = 8u << log2acc;
+      for (int rb = 0; rb < rows; rb += kRowChunk) {
+        const int re = min(rows, rb + kRowChunk);
+        if (rb > 0) __syncthreads();  // the last chunk's readers are done
+        if (range == 0 || rows > kRowChunk) {
+          for (int r = rb + tid; r < re; r += NT) {
+            uint32_t w[SB];
+            words((uint32_t)(sl.row0 + r), 0, split, s0, w);
+#pragma unroll
+            for (int s = 0; s < SB; ++s) rowt[(r - rb) * SB + s] = to_offset(w[s]);
+          }
+        }
+        __syncthreads();
+        if (!active) continue;
+        // The thread's rows of this chunk (rt + k RP across chunks, so that nxt
+        // runs on).
+        for (int r = rb + ((rt - rb) % RP + RP) % RP; r < re; r += U * RP) {
+          Q cur[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+          // the next round's rows, or the first ones of the next chunk, or of
+          // the next range or batch
+          int rn_ = r + U * RP;
+          if (rn_ >= re) {
+            if (re < rows) rn_ = re + ((rt - re) % RP + RP) % RP;
+            if (rn_ >= rows) rn_ = rt;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) nxt[u] = load(rn_ + u * RP);
+          uint32_t hv[2][SB];
+          load_row<SB>(rowt + (r - rb) * SB, hv[0]);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int ru = r + u * RP;
+            if (u + 1 < U) load_row<SB>(rowt + (min(ru + RP, re - 1) - rb) * SB, hv[(u + 1) & 1]);
+            if (ru < re) {
+              const uint32_t *h = hv[u & 1];
+              if constexpr (BANKS == 2) {
+                long long t[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                  t[i] = __double_as_longlong(fma((double)to_acc_any((T)cur[u][i]), scq[i], kMagic)) - kMagicBits;
+#pragma unroll
+                for (int s = 0; s < SB; ++s)
+#pragma unroll
+                  for (int i = 0; i < 4; ++i) add(((h[s] + lv[s][i]) & amask) | soff[s], t[i]);
+              } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                  for (int s = 0; s < SB; ++s) {
+                    const uint32_t a = h[s] + lv[s][i];
+                    const double x = (double)flip_sign(to_acc_any((T)cur[u][i]), a & kSignBit);
+                    const long long t = __double_as_longlong(fma(x, scq[i], kMagic)) - kMagicBits;
+                    if constexpr (RANGED) {
+                      const uint32_t o = (a & amask) ^ rlo;
+                      if (o < rlen) add(o + soff[0], t);
+                    } else {
+                      add((a & amask) | soff[s], t);
+                    }
+                  }
+                }
+              }
+            }
+          }
+        }
+      }
+      __syncthreads();
+      if (range == nranges - 1) put(batch + 1);
+      // Sketches out, accumulators cleared: (positive bank minus negative bank)
+      // 2^-scale, four buckets per thread and 16-byte accesses when a sketch
+      // has at least four.
+      const int lga = RANGED ? log2acc : log2m;
+      const uint32_t r0 = (uint32_t)range << log2acc;  // first bucket of the range
+      const int nsb = (int)min((int64_t)SB, samples - s0);
+      auto value = [&](unsigned long long p, unsigned long long neg) {
+        return (A)ldexp((double)(long long)(p - neg), -scale);
+      };
+      if (lga >= 2) {
+        for (int i4 = tid; i4 < (SB << (lga - 2)); i4 += NT) {
+          const int i = 4 * i4, s = i >> lga, b = i & ((1 << lga) - 1);
+          ulonglong2 *ap = reinterpret_cast<ulonglong2 *>(acc + i);
+          const ulonglong2 p0 = ap[0], p1 = ap[1];
+          ap[0] = ap[1] = make_ulonglong2(0ull, 0ull);
+          ulonglong2 n0 = make_ulonglong2(0ull, 0ull), n1 = n0;
+          if constexpr (BANKS == 2) {
+            ulonglong2 *an = reinterpret_cast<ulonglong2 *>(acc + i + signbit / 8);
+            n0 = an[0];
+            n1 = an[1];
+            an[0] = an[1] = make_ulonglong2(0ull, 0ull);
+          }
+          if (s < nsb) {
+            const A v0 = value(p0.x, n0.x), v1 = value(p0.y, n0.y), v2 = value(p1.x, n1.x), v3 = value(p1.y, n1.y);
+            A *dst = ybuf + ((s0 + s) * n_slots + sid) * (int64_t)m + r0 + b;
+            if constexpr (sizeof(A) == 4) {
+              *reinterpret_cast<float4 *>(dst) = make_float4(v0, v1, v2, v3);
+            } else {
+              reinterpret_cast<double2 *>(dst)[0] = make_double2(v0, v1);
+              reinterpret_cast<double2 *>(dst)[1] = make_double2(v2, v3);
+            }
+          }
+        }
+      } else {
+        for (int i = tid; i < (SB << lga); i += NT) {
+          const unsigned long long p = acc[i], neg = BANKS == 2 ? acc[i + signbit / 8] : 0ull;
+          acc[i] = 0ull;
+          if constexpr (BANKS == 2) acc[i + signbit / 8] = 0ull;
+          if ((i >> lga) < nsb)
+            ybuf[((s0 + (i >> lga)) * n_slots + sid) * (int64_t)m + (i & ((1 << lga) - 1))] = value(p, neg);
+        }
+      }
+    }
+  }
+}
+
+// Slots of at most kSmallSlot entries (and at most four modes of together at
+// most kStageWords indices): a wave takes one sample at a time on its own, so
+// nothing waits at a block barrier.  Its lanes hold the slot's entries and,
+// packed, the positions of their modes' hash words, for all of the wave's
+// samples; per sample they stage the words, add the entries to the wave's m
+// accumulators and write the sketch out, clearing the accumulators for the
+// next sample.  The same fixed point, bit for bit, as m1_scatter_kernel.
+// What bounds it: writing the m-word sketches of tensors of far fewer entries.
+template <typename T, typename A>
+__global__ __launch_bounds__(256) void m1_scatter_small_kernel(
+    const ScatterSlot *__restrict__ slots, int32_t n, const ModeDesc *__restrict__ modes,
+    const void *const *__restrict__ data, const int32_t *__restrict__ tables, int64_t W, int64_t samples,
+    int log2m, int64_t n_slots, A *__restrict__ ybuf, int32_t gs, int32_t groups, int32_t gx) {
+  constexpr int K = kSmallSlot / 64, KW = kStageWords / 64;
+  static_assert(kStageWords <= 255 && kStageWords % 64 == 0, "word positions are packed in bytes");
+  extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t blk = blockIdx.x / (8u * (uint32_t)gx), rem = blockIdx.x - blk * 8u * (uint32_t)gx;
+  const int32_t pos = (int32_t)(blk * 8u + (rem & 7u));
+  const int32_t grp = (int32_t)(rem >> 3) + (int32_t)blockIdx.y * gx;
+  if (pos >= n || grp >= groups) return;  // padding of the grid
+  const ScatterSlot sl = slots[pos];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t m = 1u << log2m, mask = m - 1, abytes = max(8u * m, 16u);
+  unsigned char *mine = smem + (size_t)wave * (abytes + kStageWords * 4);
+  unsigned long long *acc = reinterpret_cast<unsigned long long *>(mine);
+  uint32_t *stage = reinterpret_cast<uint32_t *>(mine + abytes);
+  const int N = sl.rows * sl.L, q = sl.q;
+  const T *X = reinterpret_cast<const T *>(data[sl.tensor]) + sl.row0 * (int64_t)sl.L;
+  const int64_t s_end = min(samples, (int64_t)(grp + 1) * gs * 4);
+  int64_t s = (int64_t)grp * gs * 4 + wave;
+
+  using XA = decltype(to_acc_any(T{}));
+  XA x[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (64 * k < N) x[k] = lane + 64 * k < N ? to_acc_any(X[lane + 64 * k]) : (XA)0;
+  int mn[4], mo[4], tot = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    mn[j] = j < q ? modes[sl.mode0 + j].n : 1;
+    mo[j] = tot;
+    tot += j < q ? mn[j] : 0;
+  }
+  // the lane's staged words: table offset and complement flag
+  int64_t w_off[KW];
+  bool w_comp[KW];
+#pragma unroll
+  for (int i = 0; i < KW; ++i) {
+    const int w = lane + 64 * i;
+    w_off[i] = 0;
+    w_comp[i] = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j < q && w >= mo[j] && w < tot) {
+        const ModeDesc md = modes[sl.mode0 + j];
+        w_off[i] = md.table_off + (w - mo[j]);
+        w_comp[i] = md.comp != 0;
+      }
+  }
+  uint32_t pre[KW];
+  auto fetch = [&](int64_t t) {
+#pragma unroll
+    for (int i = 0; i < KW; ++i)
+      if (64 * i < tot) pre[i] = lane + 64 * i < tot ? (uint32_t)tables[t * W + w_off[i]] : 0u;
+  };
+  if (s < s_end) fetch(s);
+  // word positions of the lane's entries, 8 bits per mode
+  uint32_t at[K];
+  {
+    const float rn[4] = {1.0f / (float)mn[0], 1.0f / (float)mn[1], 1.0f / (float)mn[2], 1.0f / (float)mn[3]};
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (64 * k < N) {
+        uint32_t idx = (uint32_t)(sl.row0 * sl.L) + (uint32_t)min(lane + 64 * k, N - 1);
+        at[k] = 0;
+#pragma unroll
+        for (int j = 3; j >= 0; --j)
+          if (j < q) {
+            const uint32_t qt = j > 0 ? (uint32_t)(((float)idx + 0.5f) * rn[j]) : 0u;  // idx < 2^21
+            at[k] |= (uint32_t)(mo[j] + (int)(idx - qt * (uint32_t)mn[j])) << (8 * j);
+            idx = qt;
+          }
+      }
+  }
+  double lmax = 0.0;
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (64 * k < N) lmax = fmax(lmax, fabs((double)x[k]));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) lmax = fmax(lmax, __shfl_xor(lmax, off, 64));
+  int scale = 0;
+  if (lmax > 0.0) {
+    int e;
+    (void)frexp(lmax, &e);  // max|x| < 2^e
+    scale = 62 - 11 - e;    // N <= 2^11 (see m1_scatter_kernel)
+  }
+  const double sc = ldexp(1.0, scale);
+  constexpr double kMagic = 6755399441055744.0;
+  const long long kMagicBits = __double_as_longlong(kMagic);
+  for (uint32_t i = lane; i < abytes / 16; i += 64) reinterpret_cast<uint4 *>(acc)[i] = make_uint4(0u, 0u, 0u, 0u);
+  // The wave's own LDS operations complete in order; the fences keep the
+  // compiler from moving them across each other.
+  auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  for (; s < s_end; s += 4) {
+#pragma unroll
+    for (int i = 0; i < KW; ++i)
+      if (64 * i < tot) {
+        uint32_t h = pre[i] & ~kSignBit;
+        if (w_comp[i]) h = (m - h) & mask;
+        stage[lane + 64 * i] = (h << 3) | (pre[i] & kSignBit);
+      }
+    if (s + 4 < s_end) fetch(s + 4);
+    fence();
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (64 * k < N) {
+        uint32_t a = stage[at[k] & 255u];
+        if (q > 1) a += stage[(at[k] >> 8) & 255u];
+        if (q > 2) a += stage[(at[k] >> 16) & 255u];
+        if (q > 3) a += stage[at[k] >> 24];
+        const long long t = __double_as_longlong(fma((double)flip_sign(x[k], a & kSignBit), sc, kMagic)) - kMagicBits;
+        if (lane + 64 * k < N)
+          __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(mine + (a & (mask << 3))),
+                                 (unsigned long long)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    fence();
+    A *dst = ybuf + (s * n_slots + sl.pad) * (int64_t)m;
+    auto value = [&](unsigned long long t) { return (A)ldexp((double)(long long)t, -scale); };
+    if (log2m >= 2) {
+      for (uint32_t i4 = lane; i4 < m / 4; i4 += 64) {
+        ulonglong2 *ap = reinterpret_cast<ulonglong2 *>(acc + 4 * i4);
+        const ulonglong2 p0 = ap[0], p1 = ap[1];
+        ap[0] = ap[1] = make_ulonglong2(0ull, 0ull);
+        if constexpr (sizeof(A) == 4) {
+          reinterpret_cast<float4 *>(dst)[i4] = make_float4(value(p0.x), value(p0.y), value(p1.x), value(p1.y));
+        } else {
+          reinterpret_cast<double2 *>(dst)[2 * i4] = make_double2(value(p0.x), value(p0.y));
+          reinterpret_cast<double2 *>(dst)[2 * i4 + 1] = make_double2(value(p1.x), value(p1.y));
+        }
+      }
+    } else if ((uint32_t)lane < m) {
+      dst[lane] = value(acc[lane]);
+      acc[lane] = 0ull;
+    }
+    fence();
   }
 }
 
@@ -576,56 +1059,66 @@ __global__ void twiddle_kernel(int64_t m, typename Cplx<A>::type *out) {
 
 constexpr size_t kWideLds = 81920;
 
+// One launch over the slots that are not small and all batches of SB samples.
+// A block takes `gs` batches: 16 samples where that leaves 2048 blocks (the
+// block's start is shared by all of them), fewer otherwise.  More than 16 leave
+// too few blocks of one slot side by side on an XCD to share its entries in
+// the L2 (256 lattices of bond 16, 32 samples: 2.83 ms per call with 16 samples
+// per block, 2.96 with 32).
+constexpr int64_t kSlotBlocks = 2048, kBlockSamples = 16;
+template <typename T, typename A, int SB, int BANKS, int NT, bool RANGED = false>
+int scatter_launch(const M1Launch &L, hipStream_t st) {
+  const int64_t n = L.n_big;
+  if (n == 0) return TN_OK;
+  auto kern = m1_scatter_kernel<T, A, SB, BANKS, NT, RANGED>;
+  const size_t lds = m1_scatter_lds(SB, BANKS, L.log2m);
+  if (lds > 65536)
+    TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  const int64_t batches = (L.samples + SB - 1) / SB;
+  const int64_t gs = std::max<int64_t>(1, std::min({batches, kBlockSamples / SB, n * batches / kSlotBlocks}));
+  const int64_t groups = (batches + gs - 1) / gs;
+  // groups per grid row: the grid's x extent stays within 2^31 threads
+  const int64_t slots8 = (n + 7) / 8 * 8;
+  const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(groups, ((int64_t)1 << 21) / slots8));
+  const dim3 grid((unsigned)(slots8 * gx), (unsigned)((groups + gx - 1) / gx));
+  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, L.slots, (int32_t)n, L.modes, L.data, L.tables, L.W,
+                     L.samples, L.log2m, L.n_slots, reinterpret_cast<A *>(L.ybuf),
+                     L.record_bound ? nullptr : L.slot_bound, L.slot_bound, (int32_t)gs, (int32_t)groups,
+                     (int32_t)gx);
+  TN_HIP_CHECK(hipGetLastError());
+  return TN_OK;
+}
+
 template <typename T, typename A, int SB>
 int scatter_sb(const M1Launch &L, hipStream_t st) {
   const bool ranged = L.log2m > kMaxLog2Acc;
   if (ranged && (SB != 1 || L.banks != 1))
     return set_error(TN_ERR_ARG, "scatter: m = 2^%d takes one bank and one sample per pass", L.log2m);
-  if constexpr (SB * (16 / (int)sizeof(T)) > kMaxScatterWords) {
-    return set_error(TN_ERR_UNSUPPORTED, "scatter: %d samples per pass of %d-byte data", SB, (int)sizeof(T));
-  } else {
-    // One block per CU when its LDS exceeds half a CU's: then 1024 threads, or
-    // 512 where a thread's SB x (entries per 16-byte load) table words would
-    // not fit the 128 registers of a 1024-thread block.
-    constexpr int kWideNT = SB * (16 / (int)sizeof(T)) <= 16 ? 1024 : 512;
-    const bool wide = ranged || L.lds_bytes > kWideLds;
-    auto kern = wide ? (L.banks == 2 ? m1_scatter_kernel<T, A, SB, 2, false, kWideNT>
-                                     : m1_scatter_kernel<T, A, SB, 1, false, kWideNT>)
-                     : (L.banks == 2 ? m1_scatter_kernel<T, A, SB, 2> : m1_scatter_kernel<T, A, SB, 1>);
-    if constexpr (SB == 1)
-      if (ranged) kern = m1_scatter_kernel<T, A, 1, 1, true, 1024>;
-    if (L.lds_bytes > 65536)
-      TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)L.lds_bytes));
-    // Slot bounds: without a bound array every block keeps a running
-    // maximum.  Else the first sample batch keeps one and records each slot's
-    // bound (when this launch is the first to see the data), and the other
-    // batches, in a second launch on the same stream, start from it.
-    const unsigned batches = (unsigned)((L.samples + SB - 1) / SB);
-    const unsigned z = ranged ? 1u << (L.log2m - kMaxLog2Acc) : 1u;
-    const dim3 block(ranged ? 1024 : wide ? kWideNT : 256 * L.banks);
-    A *y = reinterpret_cast<A *>(L.ybuf);
-    if (L.slot_bound == nullptr) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)L.n_slots, batches, z), block, L.lds_bytes, st, L.slots, L.modes,
-                         L.data, L.tables, L.W, L.samples, L.log2m, kMaxLog2Acc, L.n_slots, y, nullptr, nullptr, 0);
-      TN_HIP_CHECK(hipGetLastError());
-      return TN_OK;
-    }
-    int y0 = 0;
-    if (L.record_bound) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)L.n_slots, 1u, z), block, L.lds_bytes, st, L.slots, L.modes, L.data,
-                         L.tables, L.W, L.samples, L.log2m, kMaxLog2Acc, L.n_slots, y, nullptr, L.slot_bound, 0);
-      TN_HIP_CHECK(hipGetLastError());
-      y0 = 1;
-    }
-    if (batches > (unsigned)y0) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)L.n_slots, batches - (unsigned)y0, z), block, L.lds_bytes, st,
-                         L.slots, L.modes, L.data, L.tables, L.W, L.samples, L.log2m, kMaxLog2Acc, L.n_slots, y,
-                         L.slot_bound, nullptr, y0);
-      TN_HIP_CHECK(hipGetLastError());
-    }
-    return TN_OK;
-  }
+  if constexpr (SB == 1)
+    if (ranged) return scatter_launch<T, A, 1, 1, 1024, true>(L, st);
+  // 1024 threads when a block's LDS leaves no room for a second one on its
+  // CU, so that the CU still runs 16 waves; else 512.
+  const bool wide = m1_scatter_lds(SB, L.banks, L.log2m) > kWideLds;
+  int rc;
+  if (wide)
+    rc = L.banks == 2 ? scatter_launch<T, A, SB, 2, 1024>(L, st) : scatter_launch<T, A, SB, 1, 1024>(L, st);
+  else
+    rc = L.banks == 2 ? scatter_launch<T, A, SB, 2, 512>(L, st) : scatter_launch<T, A, SB, 1, 512>(L, st);
+  if (rc != TN_OK || L.n_big == L.n_slots) return rc;
+  // small slots: four samples at a time per block, one per wave
+  const int64_t n = L.n_slots - L.n_big, steps = (L.samples + 3) / 4;
+  const int64_t gs = std::max<int64_t>(1, std::min({steps, kBlockSamples / 4, n * steps / kSlotBlocks}));
+  const int64_t groups = (steps + gs - 1) / gs, slots8 = (n + 7) / 8 * 8;
+  const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(groups, ((int64_t)1 << 21) / slots8));
+  const size_t lds = 4 * (std::max<size_t>((size_t)8 << L.log2m, 16) + kStageWords * 4);
+  auto kern = m1_scatter_small_kernel<T, A>;
+  if (lds > 65536)
+    TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kern, dim3((unsigned)(slots8 * gx), (unsigned)((groups + gx - 1) / gx)), dim3(256), lds, st,
+                     L.slots + L.n_big, (int32_t)n, L.modes, L.data, L.tables, L.W, L.samples, L.log2m, L.n_slots,
+                     reinterpret_cast<A *>(L.ybuf), (int32_t)gs, (int32_t)groups, (int32_t)gx);
+  TN_HIP_CHECK(hipGetLastError());
+  return TN_OK;
 }
 
 template <typename T, typename A>
@@ -635,7 +1128,6 @@ int scatter_t(const M1Launch &L, hipStream_t st) {
     case 2: return scatter_sb<T, A, 2>(L, st);
     case 4: return scatter_sb<T, A, 4>(L, st);
     case 8: return scatter_sb<T, A, 8>(L, st);
-    case 16: return scatter_sb<T, A, 16>(L, st);
     default: return set_error(TN_ERR_ARG, "scatter: unsupported sample batch %d", L.sb);
   }
 }
@@ -723,6 +1215,12 @@ int combine_t(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
 }
 
 }  // namespace
+
+size_t m1_scatter_lds(int sb, int banks, int log2m) {
+  const size_t ma = (size_t)1 << std::min(log2m, kMaxLog2Acc);  // bucket ranges above
+  const size_t acc = banks == 2 ? sign_bank_bytes(sb, (uint32_t)ma) : (size_t)sb * 8 * ma;
+  return ((acc + 15) & ~(size_t)15) + (size_t)sb * 4 * (kRowChunk + kStageWords) + 16;
+}
 
 int launch_m1_scatter(const M1Launch &L, hipStream_t st) {
   if (L.n_slots == 0 || L.samples == 0) return TN_OK;

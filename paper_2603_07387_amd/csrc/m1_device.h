@@ -104,7 +104,6 @@ struct FixedScale {
   double bound = 0.0;  // every |x| seen is < bound (0: none seen yet)
   int lgN = 11;        // >= ceil(log2(terms)) and >= 11
   int par = 0;         // parity of the double-buffered running maximum
-  bool known = false;  // bound given up front: no running maximum
 };
 
 // Layout of SB two-bank sketches of m words: positive banks of the SB samples
@@ -133,26 +132,13 @@ __host__ __device__ constexpr size_t sign_bank_bytes(int sb, uint32_t m) {
 // loads.  s_max (2 words of LDS) holds the running maximum; both it and fs
 // carry over between calls that feed the same sketches.  All NT threads of
 // the block call it; it starts and ends with a barrier.
-// fresh (optional): the accumulators, fresh_words 4-byte words, not yet
-// cleared; the column tables are then built from the modes' hash words staged
-// there, and the accumulators are cleared before the scatter.  Without it the
-// caller clears them.
-// RANGED (one bank): the LDS holds only the 2^log2acc buckets starting at
-// bucket rsel * 2^log2acc of each sketch; terms outside that range are
-// dropped.  Every range sees the same terms in the same order, so all ranges
-// of a slot reach the same fixed-point scale.
-template <typename T, int SB, int BANKS, int NT, bool RANGED = false>
+template <typename T, int SB, int BANKS, int NT>
 __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDesc *__restrict__ modes,
                                              const void *const *__restrict__ data,
                                              const int32_t *__restrict__ tables, int64_t W, int nsb,
                                              int log2m, unsigned long long *acc, uint32_t sbytes,
                                              uint32_t signbit, uint32_t *tabs,
-                                             unsigned long long *s_max, FixedScale &fs, uint32_t rsel = 0,
-                                             int log2acc = -1, uint32_t *fresh = nullptr,
-                                             uint32_t fresh_words = 0) {
-  static_assert(!RANGED || BANKS == 1, "bucket ranges use one bank");
-  if (log2acc < 0) log2acc = log2m;
-  const uint32_t rshift = 3u + (uint32_t)log2acc;  // byte offset >> rshift = range index
+                                             unsigned long long *s_max, FixedScale &fs) {
   const int tid = threadIdx.x;
   const uint32_t m = 1u << log2m, mask = m - 1;
   const int L = sl.L, rows = sl.rows;
@@ -173,52 +159,9 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
   };
   __syncthreads();  // earlier readers of the tables are done
   const int uc0 = sl.mode0 + sl.split, uc1 = sl.mode0 + sl.q - 1;  // column modes
-  int qc = 0;  // their hash words per sample
-  for (int u = uc0; u <= uc1; ++u) qc += modes[u].n;
-  if (fresh != nullptr && (uint32_t)(nsb * qc) <= fresh_words) {
-    // The column modes' hash words of the nsb samples, complement applied,
-    // staged in the (not yet cleared) accumulator LDS: sample s, mode u,
-    // index d at fresh[s qc + off_u + d], modes in order.  One global read
-    // per word instead of one per (column, mode).
-    for (int i = tid; i < nsb * qc; i += NT) {
-      const int s = i / qc;
-      int d = i - s * qc, u = uc0;
-      while (d >= modes[u].n) d -= modes[u++].n;
-      const ModeDesc md = modes[u];
-      const uint32_t v = (uint32_t)tables[s * W + md.table_off + d];
-      uint32_t h = v & ~kSignBit;
-      if (md.comp) h = (m - h) & mask;
-      fresh[i] = h | (v & kSignBit);
-    }
-    __syncthreads();
-    // Column c's word per sample: the digits of c mod L, last mode fastest,
-    // found once for all samples.
-    for (int c = tid; c < Lb; c += NT) {
-      uint32_t idx = (uint32_t)(c < L ? c : c % L), w[SB];
-#pragma unroll
-      for (int s = 0; s < SB; ++s) w[s] = 0;
-      int off = qc;
-      for (int u = uc1; u >= uc0; --u) {
-        const uint32_t n = (uint32_t)modes[u].n;
-        off -= (int)n;
-        const uint32_t d = idx % n;
-        idx /= n;
-#pragma unroll
-        for (int s = 0; s < SB; ++s)
-          if (s < nsb) {
-            const uint32_t v = fresh[s * qc + off + d];
-            w[s] = (((w[s] & ~kSignBit) + (v & ~kSignBit)) & mask) | ((w[s] ^ v) & kSignBit);
-          }
-      }
-#pragma unroll
-      for (int s = 0; s < SB; ++s)
-        if (s < nsb) colt[s * Lp + c] = to_offset(w[s]);
-    }
-  } else {
-    for (int i = tid; i < nsb * Lb; i += NT) {
-      const int s = i / Lb, c = i - s * Lb;
-      colt[s * Lp + c] = to_offset(combine_modes(tables + s * W, modes, uc0, uc1, c < L ? c : c % L, m, mask));
-    }
+  for (int i = tid; i < nsb * Lb; i += NT) {
+    const int s = i / Lb, c = i - s * Lb;
+    colt[s * Lp + c] = to_offset(combine_modes(tables + s * W, modes, uc0, uc1, c < L ? c : c % L, m, mask));
   }
   for (int i = tid; i < nsb * rows; i += NT) {
     const int s = i / rows, r = i - s * rows;
@@ -226,10 +169,6 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
                                                  (uint32_t)(sl.row0 + r), m, mask));
   }
   __syncthreads();
-  if (fresh != nullptr) {  // clear the accumulators (they held the staged words)
-    lds_zero(fresh, fresh_words * 4u, tid, NT);
-    __syncthreads();
-  }
   const uint32_t amask = (mask << 3) | (BANKS == 2 ? signbit : 0u);
   char *acc8 = reinterpret_cast<char *>(acc);
   // The slot's entries as 16-byte vectors: from the start when every row is a
@@ -237,11 +176,7 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
   // from the first aligned vector (the entries before it and after the last
   // whole vector are read singly).
   using V = typename Vec16<T>::type;
-  // 16-byte loads in flight per thread: 8 in the 512-thread blocks (two per CU,
-  // registers to spare; half the barriers per entry), else 4; 4 in the
-  // unaligned loop (its tables take the registers)
-  constexpr int UNROLL = NT == 512 && SB * VEC <= 16 ? 8 : 4;
-  constexpr int UNW = 4;
+  constexpr int UNROLL = 4;  // 16-byte loads in flight per thread
   const T *X = reinterpret_cast<const T *>(data[sl.tensor]) + sl.row0 * (int64_t)L;
   const uint32_t N = (uint32_t)rows * (uint32_t)L;
   const bool vec = (L % VEC == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
@@ -253,10 +188,8 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
 
   // Block-wide running max of |x| (double-buffered so the read of one
   // iteration cannot race with the next iteration's update), then a rescale
-  // when it reaches the bound.  Called by every thread once per iteration,
-  // unless the block starts from a known bound.
+  // when it reaches the bound.  Called by every thread once per iteration.
   auto update_scale = [&](double lmax) {
-    if (fs.known) return;  // uniform over the block
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) lmax = fmax(lmax, __shfl_xor(lmax, off, 64));
     if ((tid & 63) == 0) atomicMax(&s_max[fs.par], (unsigned long long)__double_as_longlong(lmax));
@@ -269,9 +202,9 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
       const int ns = 62 - fs.lgN - e;
       if (fs.bound > 0.0 && fs.scale > ns) {
         const int d = fs.scale - ns;
-        for (int i = tid; i < (BANKS * nsb) << log2acc; i += NT) {
-          const int si = BANKS == 2 ? i >> (log2acc + 1) : i >> log2acc;
-          const int bank = BANKS == 2 ? (i >> log2acc) & 1 : 0, b = i & ((1 << log2acc) - 1);
+        for (int i = tid; i < (BANKS * nsb) << log2m; i += NT) {
+          const int si = BANKS == 2 ? i >> (log2m + 1) : i >> log2m;
+          const int bank = BANKS == 2 ? (i >> log2m) & 1 : 0, b = i & ((1 << log2m) - 1);
           unsigned long long *w = reinterpret_cast<unsigned long long *>(
               reinterpret_cast<char *>(acc) + (size_t)si * sbytes + (bank ? signbit : 0u)) + b;
           *w = (unsigned long long)((long long)*w >> d);
@@ -292,13 +225,6 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
   // One fixed-point add into sample s's sketch (its sign selects the bank).
   // (nv = -v, formed once per entry for all samples of the batch.)
   auto add_fixed = [&](int s, uint32_t hv, uint32_t lv, long long v, long long nv) {
-    if constexpr (RANGED) {
-      const uint32_t o = (hv + lv) & amask;
-      if ((o >> rshift) != rsel) return;
-      atomicAdd(reinterpret_cast<unsigned long long *>(acc8 + (o & ((1u << rshift) - 1u)) + (uint32_t)s * sbytes),
-                (unsigned long long)(((hv ^ lv) & kSignBit) ? nv : v));
-      return;
-    }
     const uint32_t a = ((hv + lv) & amask) + (uint32_t)s * sbytes;
     if constexpr (BANKS == 2)
       atomicAdd(reinterpret_cast<unsigned long long *>(acc8 + a), (unsigned long long)v);
@@ -330,141 +256,48 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
     // the VEC entries of one load share a row.
     // Unconditional loads (index clamped into the slot) keep all UNROLL loads
     // in flight; out-of-range lanes are masked when the values are used.
-    // Blocks of 512 or more threads (few blocks per CU: their LDS is large)
-    // issue the next iteration's loads before this iteration's adds, so the
-    // load latency hides behind the LDS atomics; small blocks overlap with
-    // other blocks instead and keep the registers.
-    constexpr bool PREFETCH = NT >= 512;
-    if constexpr (NT == 512) {
-      // 512-thread blocks: when NT * VEC is a multiple of the row length, every
-      // vector a thread loads starts at the same column (tid * VEC) mod L, so
-      // its column-table entries are read once, not once per vector (a third
-      // of the loop's LDS bytes otherwise).  The loop is instantiated for both
-      // cases; blocks of other sizes keep the general loop below (they have no
-      // registers to spare for a second instantiation).
-      auto vec_loop = [&](auto FIXED_) {
-        constexpr bool FIXED = decltype(FIXED_)::value;
-        uint32_t lvf[SB][VEC];
-        if constexpr (FIXED) {
+    V buf[UNROLL];
+    for (uint32_t v0 = 0; v0 < NV; v0 += NT * UNROLL) {
 #pragma unroll
-          for (int s = 0; s < SB; ++s) load_cols<VEC>(colt + s * Lp + ((uint32_t)tid * VEC) % (uint32_t)L, lvf[s]);
+      for (int u = 0; u < UNROLL; ++u) buf[u] = Xv[min(v0 + u * NT + tid, NV - 1)];
+      {  // running maximum of this load round
+        double lmax = 0.0;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+          const T *xs = reinterpret_cast<const T *>(&buf[u]);
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) lmax = fmax(lmax, fabs((double)to_acc_any(xs[i])));
         }
-        V buf[UNROLL], nxt[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) nxt[u] = Xv[min((uint32_t)(u * NT + tid), NV - 1)];
-        for (uint32_t v0 = 0; v0 < NV; v0 += NT * UNROLL) {
-#pragma unroll
-          for (int u = 0; u < UNROLL; ++u) buf[u] = nxt[u];
-          if (!fs.known) {  // running maximum of this load round (uniform over the block)
-            double lmax = 0.0;
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-              const T *xs = reinterpret_cast<const T *>(&buf[u]);
-#pragma unroll
-              for (int i = 0; i < VEC; ++i) lmax = fmax(lmax, fabs((double)to_acc_any(xs[i])));
-            }
-            update_scale(lmax);
-          }
-          if (v0 + NT * UNROLL < NV) {  // uniform over the block
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) nxt[u] = Xv[min(v0 + (u + UNROLL) * NT + tid, NV - 1)];
-          }
-          uint32_t rr[UNROLL], cc[UNROLL];
-#pragma unroll
-          for (int u = 0; u < UNROLL; ++u) {
-            const uint32_t e = min(v0 + u * NT + tid, NV - 1) * VEC;  // clamped: valid table reads
-            rr[u] = (L == 1) ? e : __umulhi(e, sl.magic);
-            cc[u] = e - rr[u] * (uint32_t)L;
-          }
-          // the table reads of vector u + 1 are issued before the adds of vector u
-          uint32_t hv[2][SB], lv[2][SB][VEC];
-          auto tabs = [&](int u, int k) {
-            if constexpr (FIXED) {
-#pragma unroll
-              for (int s = 0; s < SB; ++s) hv[k][s] = rowt[s * rows + rr[u]];
-            } else {
-              read_tabs(rr[u], cc[u], hv[k], lv[k]);
-            }
-          };
-          tabs(0, 0);
-#pragma unroll
-          for (int u = 0; u < UNROLL; ++u) {
-            if (u + 1 < UNROLL) tabs(u + 1, (u + 1) & 1);
-            if (v0 + u * NT + tid < NV) {
-              const T *xs = reinterpret_cast<const T *>(&buf[u]);
-              long long q[VEC], nq[VEC];
-#pragma unroll
-              for (int i = 0; i < VEC; ++i) {
-                q[i] = to_fixed((double)to_acc_any(xs[i]));
-                nq[i] = BANKS == 2 ? 0 : -q[i];
-              }
-#pragma unroll
-              for (int s = 0; s < SB; ++s)
-                if (s < nsb) {
-#pragma unroll
-                  for (int i = 0; i < VEC; ++i)
-                    add_fixed(s, hv[u & 1][s], FIXED ? lvf[s][i] : lv[u & 1][s][i], q[i], nq[i]);
-                }
-            }
-          }
-        }
-      };
-      if (((uint32_t)(NT * VEC)) % (uint32_t)L == 0)
-        vec_loop(std::true_type{});
-      else
-        vec_loop(std::false_type{});
-    } else {
-      V buf[UNROLL], nxt[UNROLL];
-      if constexpr (PREFETCH) {
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) nxt[u] = Xv[min((uint32_t)(u * NT + tid), NV - 1)];
+        update_scale(lmax);
       }
-      for (uint32_t v0 = 0; v0 < NV; v0 += NT * UNROLL) {
+      uint32_t rr[UNROLL], cc[UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) buf[u] = PREFETCH ? nxt[u] : Xv[min(v0 + u * NT + tid, NV - 1)];
-        if (!fs.known) {  // running maximum of this load round (uniform over the block)
-          double lmax = 0.0;
+      for (int u = 0; u < UNROLL; ++u) {
+        const uint32_t e = min(v0 + u * NT + tid, NV - 1) * VEC;  // clamped: valid table reads
+        rr[u] = (L == 1) ? e : __umulhi(e, sl.magic);
+        cc[u] = e - rr[u] * (uint32_t)L;
+      }
+      // Software pipeline: the table reads of vector u + 1 are issued before the
+      // adds of vector u.
+      uint32_t hv[2][SB], lv[2][SB][VEC];
+      read_tabs(rr[0], cc[0], hv[0], lv[0]);
 #pragma unroll
-          for (int u = 0; u < UNROLL; ++u) {
-            const T *xs = reinterpret_cast<const T *>(&buf[u]);
+      for (int u = 0; u < UNROLL; ++u) {
+        if (u + 1 < UNROLL) read_tabs(rr[u + 1], cc[u + 1], hv[(u + 1) & 1], lv[(u + 1) & 1]);
+        if (v0 + u * NT + tid < NV) {
+          const T *xs = reinterpret_cast<const T *>(&buf[u]);
+          long long q[VEC], nq[VEC];
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) lmax = fmax(lmax, fabs((double)to_acc_any(xs[i])));
+          for (int i = 0; i < VEC; ++i) {
+            q[i] = to_fixed((double)to_acc_any(xs[i]));
+            nq[i] = BANKS == 2 ? 0 : -q[i];
           }
-          update_scale(lmax);
-        }
-        if (PREFETCH && v0 + NT * UNROLL < NV) {  // uniform over the block
 #pragma unroll
-          for (int u = 0; u < UNROLL; ++u) nxt[u] = Xv[min(v0 + (u + UNROLL) * NT + tid, NV - 1)];
-        }
-        uint32_t rr[UNROLL], cc[UNROLL];
+          for (int s = 0; s < SB; ++s)
+            if (s < nsb) {
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          const uint32_t e = min(v0 + u * NT + tid, NV - 1) * VEC;  // clamped: valid table reads
-          rr[u] = (L == 1) ? e : __umulhi(e, sl.magic);
-          cc[u] = e - rr[u] * (uint32_t)L;
-        }
-        // Software pipeline: the table reads of vector u + 1 are issued before the
-        // adds of vector u.
-        uint32_t hv[2][SB], lv[2][SB][VEC];
-        read_tabs(rr[0], cc[0], hv[0], lv[0]);
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          if (u + 1 < UNROLL) read_tabs(rr[u + 1], cc[u + 1], hv[(u + 1) & 1], lv[(u + 1) & 1]);
-          if (v0 + u * NT + tid < NV) {
-            const T *xs = reinterpret_cast<const T *>(&buf[u]);
-            long long q[VEC], nq[VEC];
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-              q[i] = to_fixed((double)to_acc_any(xs[i]));
-              nq[i] = BANKS == 2 ? 0 : -q[i];
+              for (int i = 0; i < VEC; ++i) add_fixed(s, hv[u & 1][s], lv[u & 1][s][i], q[i], nq[i]);
             }
-#pragma unroll
-            for (int s = 0; s < SB; ++s)
-              if (s < nsb) {
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) add_fixed(s, hv[u & 1][s], lv[u & 1][s][i], q[i], nq[i]);
-              }
-          }
         }
       }
     }
@@ -489,28 +322,19 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
       }
     }
     if (NV > 0) {  // uniform over the block
-      constexpr bool PREFETCH = NT >= 512;
-      V buf[UNW], nxt[UNW];
-      if constexpr (PREFETCH) {
+      V buf[UNROLL];
+      for (uint32_t v0 = 0; v0 < NV; v0 += NT * UNROLL) {
 #pragma unroll
-        for (int u = 0; u < UNW; ++u) nxt[u] = Xv[min((uint32_t)(u * NT + tid), NV - 1)];
-      }
-      for (uint32_t v0 = 0; v0 < NV; v0 += NT * UNW) {
-#pragma unroll
-        for (int u = 0; u < UNW; ++u) buf[u] = PREFETCH ? nxt[u] : Xv[min(v0 + u * NT + tid, NV - 1)];
-        if (!fs.known) {  // running maximum of this load round (uniform over the block)
+        for (int u = 0; u < UNROLL; ++u) buf[u] = Xv[min(v0 + u * NT + tid, NV - 1)];
+        {  // running maximum of this load round
           double lmax = 0.0;
 #pragma unroll
-          for (int u = 0; u < UNW; ++u) {
+          for (int u = 0; u < UNROLL; ++u) {
             const T *xs = reinterpret_cast<const T *>(&buf[u]);
 #pragma unroll
             for (int i = 0; i < VEC; ++i) lmax = fmax(lmax, fabs((double)to_acc_any(xs[i])));
           }
           update_scale(lmax);
-        }
-        if (PREFETCH && v0 + NT * UNW < NV) {  // uniform over the block
-#pragma unroll
-          for (int u = 0; u < UNW; ++u) nxt[u] = Xv[min(v0 + (u + UNW) * NT + tid, NV - 1)];
         }
         if (L >= VEC) {  // uniform over the block: a vector spans at most two rows
           // Per sample the row words of the vector's row and of the next one
@@ -518,7 +342,7 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
           // the vector's adds; entry i takes the next row's word when column
           // c + i passes the row's end.
 #pragma unroll
-          for (int u = 0; u < UNW; ++u) {
+          for (int u = 0; u < UNROLL; ++u) {
             if (v0 + u * NT + tid < NV) {
               const uint32_t e = head + (v0 + u * NT + tid) * VEC;
               const uint32_t r = __umulhi(e, sl.magic), c = e - r * (uint32_t)L;
@@ -543,7 +367,7 @@ __device__ __forceinline__ void scatter_slot(const ScatterSlot &sl, const ModeDe
           }
         } else {  // rows shorter than a vector
 #pragma unroll
-          for (int u = 0; u < UNW; ++u) {
+          for (int u = 0; u < UNROLL; ++u) {
             if (v0 + u * NT + tid < NV) {
               const uint32_t e = head + (v0 + u * NT + tid) * VEC;
               uint32_t r = (L == 1) ? e : __umulhi(e, sl.magic);

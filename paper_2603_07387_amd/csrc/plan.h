@@ -66,7 +66,9 @@ struct tn_plan {
   std::vector<int32_t> h_tslot;  // per global tensor: first slot; n_tensors + 1 entries
   std::vector<tn::NetDesc> h_nets;
   tn::ModeDesc *d_modes = nullptr;
-  tn::ScatterSlot *d_slots = nullptr;
+  tn::ScatterSlot *d_slots = nullptr;   // (persistent kernel)
+  tn::ScatterSlot *d_sorted = nullptr;  // the slots, the largest first
+  int64_t n_big = 0;                    // of these, the ones that are not small (they come first)
   int32_t *d_tslot = nullptr;
   tn::NetDesc *d_nets = nullptr;
   void *d_tw = nullptr;
@@ -82,7 +84,6 @@ struct tn_plan {
   double *d_csplit = nullptr;   // their partial product spectra [network][sample][block][m/2 + 1] (complex)
   int sb = 1;
   int banks = 1;            // scatter accumulator banks (autotuned: 1 or 2)
-  size_t scatter_lds = 0;
   int64_t chunk = 0;        // samples per workspace pass
   int64_t chunk_alloc = 0;  // samples the workspace was sized for
   size_t worst_cols_rows = 0;

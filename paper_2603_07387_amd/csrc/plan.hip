@@ -18,7 +18,8 @@ namespace tn {
 namespace {
 
 constexpr int kMaxRowsPerSlot = 2048;
-constexpr size_t kWorkspaceBudget = (size_t)1 << 30;  // tables + sketches per pass
+constexpr size_t kWorkspaceBudget = (size_t)4 << 30;  // tables + sketches per pass (16 samples of the batch of 4096 networks: 2 GiB)
+constexpr int64_t kScatterFill = 256;  // scatter blocks to keep (one per CU) when taking more samples per pass
 constexpr int64_t kCombineSplitBlocks = 1024;            // combine blocks to aim for when splitting
 constexpr size_t kCombineSplitBudget = (size_t)256 << 20;  // bytes of partial spectra
 constexpr int64_t kCombineSplitWork = 65536;               // least (pairs x m) of a network worth splitting
@@ -47,16 +48,6 @@ int upload(T **ptr, const std::vector<T> &v) {
 }
 
 size_t acc_size(int dtype) { return dtype == TN_F64 ? sizeof(double) : sizeof(float); }
-
-// LDS of one scatter block: the fixed-point accumulators (p->banks banks of m
-// 8-byte words per sample) plus the packed tables.  (+64: the accumulator
-// block is padded to 16 bytes and the kernel keeps a 16-byte running maximum
-// in static LDS.)
-size_t scatter_lds_for(const tn_plan *p, int sb) {
-  const int64_t ma = std::min<int64_t>(p->m, (int64_t)1 << kMaxLog2Acc);  // bucket ranges above
-  const size_t acc = p->banks == 2 ? m1dev::sign_bank_bytes(sb, (uint32_t)p->m) : (size_t)sb * 8 * ma;
-  return acc + (size_t)sb * 4 * p->worst_cols_rows + 64;
-}
 
 constexpr size_t kFusedStatic = 128;  // static LDS of the persistent kernel
 
@@ -120,6 +111,7 @@ int add_tensor_slots(tn_plan *p, int32_t gtensor, int32_t mode0, int q, const in
     sl.mode0 = mode0;
     sl.rows = (int32_t)std::min<int64_t>(rows_per, R - r0);
     sl.row0 = r0;
+    sl.pad = (int32_t)p->h_slots.size();
     sl.magic = L > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)L + 1) : 0u;
     p->h_slots.push_back(sl);
   }
@@ -197,22 +189,24 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   const bool big = p->log2m > kMaxLog2Acc;  // bucket ranges in the scatter
   p->h_tslot.push_back((int32_t)p->h_slots.size());
 
-  // Samples per scatter block: as many as fit 64 KB of LDS (two blocks per CU),
-  // else one.
   size_t worst_cols_rows = 0;
   for (const ScatterSlot &sl : p->h_slots)
     worst_cols_rows = std::max(worst_cols_rows, (size_t)(sl.L + kColPad + sl.rows + 1));
-  // 64-bit fixed-point accumulators (two banks of 8-byte words per sample)
-  // plus packed tables.  (+64: the accumulator block is padded to 16 bytes and
-  // the kernel keeps a 16-byte running maximum in static LDS.)
-  // One bank with signed adds by default; TN_FLAG_AUTOTUNE also times two
-  // banks (the sign in the address: fewer ALU operations, twice the LDS).
+  // Samples per pass of the scatter: four, or two or one where the accumulators
+  // of more leave no room for two blocks per CU, and fewer where a plan has
+  // too few slots for a block on every CU (one triangle of 64 x 64, m = 256, 16
+  // samples: 23.7 us per call with one sample per pass, 25.4 with four).  One
+  // bank (three blocks per CU at m = 1024); TN_FLAG_AUTOTUNE also times two (the
+  // sign in the address: fewer vector instructions, twice the LDS).
   p->worst_cols_rows = worst_cols_rows;
   p->banks = 1;
-  auto lds_for = [&](int sb) { return scatter_lds_for(p, sb); };
+  auto lds_for = [&](int sb) { return m1_scatter_lds(sb, p->banks, p->log2m); };
   p->sb = 1;
-  for (int sb : {8, 4, 2}) {
-    if (sb <= p->S && lds_for(sb) <= 81920) { p->sb = sb; break; }
+  for (int sb : {4, 2}) {
+    if (sb <= p->S && lds_for(sb) <= 81920 && (int64_t)p->h_slots.size() * (p->S / sb) >= kScatterFill) {
+      p->sb = sb;
+      break;
+    }
   }
   // Overrides of the untuned schedule (tests and tuning experiments; the
   // autotuner, when requested, still decides).
@@ -228,14 +222,10 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   }
   if (const char *env = getenv("TN_SCATTER_SB"); env && !big) {
     const int sb = atoi(env);
-    if ((sb == 1 || sb == 2 || sb == 4 || sb == 8 || sb == 16) && lds_for(sb) <= p->max_lds &&
-        scatter_words(sb, p->dtype) <= kMaxScatterWords)
-      p->sb = sb;
+    if ((sb == 1 || sb == 2 || sb == 4 || sb == 8) && lds_for(sb) <= p->max_lds) p->sb = sb;
   }
-  p->scatter_lds = lds_for(p->sb);
-  p->worst_cols_rows = worst_cols_rows;
-  if (p->scatter_lds > p->max_lds)
-    return set_error(TN_ERR_UNSUPPORTED, "cyclic method: scatter needs %zu bytes of LDS", p->scatter_lds);
+  if (lds_for(p->sb) > p->max_lds)
+    return set_error(TN_ERR_UNSUPPORTED, "cyclic method: scatter needs %zu bytes of LDS", lds_for(p->sb));
 
   const size_t per_sample = (size_t)p->W * 4 + p->h_slots.size() * (size_t)p->m * as +
                             (p->two_pass ? (size_t)(p->n_tensors + p->n_nets) / 2 * (size_t)p->m * 2 * as +
@@ -296,7 +286,25 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   int rc;
   if ((rc = upload(&p->d_streams, p->h_streams)) != TN_OK) return rc;
   if ((rc = upload(&p->d_modes, p->h_modes)) != TN_OK) return rc;
-  if ((rc = upload(&p->d_slots, p->h_slots)) != TN_OK) return rc;
+  if (p->fused && (rc = upload(&p->d_slots, p->h_slots)) != TN_OK) return rc;
+  // The scatter's order of slots: the largest first, the small ones (one wave
+  // per sample: few entries of a tensor of few hash words) last.
+  auto small = [&](const ScatterSlot &sl) {
+    if (p->log2m > kMaxLog2Small || sl.q > 4 || (int64_t)sl.rows * sl.L > kSmallSlot) return false;
+    int64_t words = 0, size = 1;
+    for (int j = 0; j < sl.q; ++j) {
+      words += p->h_modes[(size_t)(sl.mode0 + j)].n;
+      size *= p->h_modes[(size_t)(sl.mode0 + j)].n;
+    }
+    return words <= kStageWords && size < (1 << 21);
+  };
+  std::vector<ScatterSlot> sorted = p->h_slots;
+  std::stable_sort(sorted.begin(), sorted.end(), [&](const ScatterSlot &x, const ScatterSlot &y) {
+    const bool sx = small(x), sy = small(y);
+    return sx != sy ? sy : (int64_t)x.rows * x.L > (int64_t)y.rows * y.L;
+  });
+  p->n_big = std::count_if(sorted.begin(), sorted.end(), [&](const ScatterSlot &x) { return !small(x); });
+  if ((rc = upload(&p->d_sorted, sorted)) != TN_OK) return rc;
   if ((rc = upload(&p->d_tslot, p->h_tslot)) != TN_OK) return rc;
   if ((rc = upload(&p->d_nets, p->h_nets)) != TN_OK) return rc;
   if ((rc = dev_alloc(&p->d_tables, (size_t)table_samples * (size_t)p->W)) != TN_OK) return rc;
@@ -418,7 +426,8 @@ int m1_run(tn_plan *p, hipStream_t st, double *est) {
     int rc = m1_tables(p, c0, n, st, &tables);
     if (rc != TN_OK) return rc;
     M1Launch L{};
-    L.slots = p->d_slots;
+    L.slots = p->d_sorted;
+    L.n_big = p->n_big;
     L.n_slots = (int64_t)p->h_slots.size();
     L.modes = p->d_modes;
     L.data = p->d_data;
@@ -429,7 +438,6 @@ int m1_run(tn_plan *p, hipStream_t st, double *est) {
     L.sb = p->sb;
     L.banks = p->banks;
     L.log2m = p->log2m;
-    L.lds_bytes = p->scatter_lds;
     L.ybuf = p->d_ybuf;
     L.slot_bound = p->d_slot_bound;
     L.record_bound = c0 == 0;  // the data may have changed since the last call
@@ -491,7 +499,6 @@ int m1_autotune(tn_plan *p, hipStream_t st) {
     if (p->fused) return fused_configure(p, sb, banks);
     p->sb = sb;
     p->banks = banks;
-    p->scatter_lds = scatter_lds_for(p, sb);
     return TN_OK;
   };
   {
@@ -515,20 +522,16 @@ int m1_autotune(tn_plan *p, hipStream_t st) {
   TN_HIP_CHECK(hipEventCreateWithFlags(&e1, hipEventDisableSystemFence));
   std::pair<int, int> best{p->fused ? p->fused_sb : p->sb, p->fused ? p->fused_banks : p->banks};
   float best_ms = 1e30f;
-  const int sbs_slot[] = {1, 2, 4, 8, 16}, sbs_fused[] = {1, 2, 4};
+  const int sbs_slot[] = {1, 2, 4, 8}, sbs_fused[] = {1, 2, 4};
   for (int banks : {1, 2}) {
-    for (int sb : p->fused ? std::vector<int>(sbs_fused, sbs_fused + 3) : std::vector<int>(sbs_slot, sbs_slot + 5)) {
+    for (int sb : p->fused ? std::vector<int>(sbs_fused, sbs_fused + 3) : std::vector<int>(sbs_slot, sbs_slot + 4)) {
       if (sb > 1 && sb > n) break;
       float ms = 0.f;
       if (p->fused) {
         if (m1_fused_lds(sb, banks, p->m, (int32_t)p->worst_cols_rows) + kFusedStatic > p->max_lds) break;
         if ((rc = fused_configure(p, sb, banks)) != TN_OK) break;
       } else {
-        const int save = p->banks;
-        p->banks = banks;
-        const size_t lds = scatter_lds_for(p, sb);
-        p->banks = save;
-        if (lds > p->max_lds || scatter_words(sb, p->dtype) > kMaxScatterWords) break;
+        if (m1_scatter_lds(sb, banks, p->log2m) > p->max_lds) break;
       }
       // one warm-up launch, then the faster of two timed ones
       float ms_min = 1e30f;
@@ -563,7 +566,8 @@ int m1_autotune(tn_plan *p, hipStream_t st) {
             rc = launch_m1_fused(L, st);
           } else {
             M1Launch L{};
-                    L.slots = p->d_slots;
+            L.slots = p->d_sorted;
+            L.n_big = p->n_big;
             L.n_slots = (int64_t)p->h_slots.size();
             L.modes = p->d_modes;
             L.data = p->d_data;
@@ -574,8 +578,6 @@ int m1_autotune(tn_plan *p, hipStream_t st) {
             L.sb = sb;
             L.banks = banks;
             L.log2m = p->log2m;
-            p->banks = banks;
-            L.lds_bytes = scatter_lds_for(p, sb);
             L.ybuf = p->d_ybuf;
             L.slot_bound = p->d_slot_bound;
             L.record_bound = true;
@@ -849,7 +851,7 @@ void plan_release(tn_plan *p) {
   void *ptrs[] = {p->d_streams, p->d_tables, p->d_injected, p->d_data,    p->d_modes,
                   p->d_slots,   p->d_tslot,  p->d_nets,     p->d_tw,      p->d_ybuf,
                   p->d_est,     p->d_items,  p->d_counter,  p->d_tensor_lgn, p->d_cbuf, p->d_partial,
-                  p->d_pairs,   p->d_pair0,  p->d_slot_bound, p->d_csplit};
+                  p->d_pairs,   p->d_pair0,  p->d_slot_bound, p->d_csplit, p->d_sorted};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   p->d_streams = nullptr;
@@ -857,6 +859,7 @@ void plan_release(tn_plan *p) {
   p->d_data = nullptr;
   p->d_modes = nullptr;
   p->d_slots = nullptr;
+  p->d_sorted = nullptr;
   p->d_tslot = nullptr;
   p->d_nets = nullptr;
   p->d_tw = p->d_ybuf = p->d_cbuf = nullptr;
@@ -999,7 +1002,8 @@ int plan_get_sketches(tn_plan *p, const tn_network *nets, int64_t first, int64_t
     const int32_t *tables = nullptr;
     if ((rc = m1_tables(p, c0, n, st, &tables)) != TN_OK) return rc;
     M1Launch L{};
-    L.slots = p->d_slots;
+    L.slots = p->d_sorted;
+    L.n_big = p->n_big;
     L.n_slots = (int64_t)p->h_slots.size();
     L.modes = p->d_modes;
     L.data = p->d_data;
@@ -1010,7 +1014,6 @@ int plan_get_sketches(tn_plan *p, const tn_network *nets, int64_t first, int64_t
     L.sb = p->sb;
     L.banks = p->banks;
     L.log2m = p->log2m;
-    L.lds_bytes = p->scatter_lds;
     L.ybuf = p->d_ybuf;
     L.slot_bound = p->d_slot_bound;
     L.record_bound = c0 == first;

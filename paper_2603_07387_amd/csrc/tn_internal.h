@@ -67,7 +67,7 @@ struct ScatterSlot {
   int32_t rows;       // rows in this block
   int64_t row0;       // first row of the block
   uint32_t magic;     // ceil(2^32 / L): row = umulhi(e, magic) for e < 2^21
-  int32_t pad;
+  int32_t pad;        // the slot's number (in the plan's order of slots)
 };
 
 // Per network: its tensors [t0, t1) and, per tensor, slots
@@ -82,17 +82,17 @@ constexpr int kColPad = 8;              // words after each sample's column tabl
 constexpr int kMaxSlotEntries = 1 << 16;  // entries per scatter block
 constexpr int kMaxLog2M1 = 16;          // m <= 65536
 constexpr size_t kMaxLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
-// Column-table words a scatter thread holds per load: samples per pass x
-// entries per 16-byte load.  Above 64 the scatter would spill registers, so
-// such schedules are not offered.
-constexpr int kMaxScatterWords = 64;
-inline int scatter_words(int sb, int dtype) { return sb * (dtype == TN_F64 ? 2 : dtype == TN_F32 ? 4 : 8); }
+constexpr int kRowChunk = 512;          // rows whose hash words a scatter block holds in LDS at a time
+constexpr int kSmallSlot = 1024;        // entries of a slot that the scatter takes one wave per sample for
+constexpr int kMaxLog2Small = 11;       // largest log2 m of those (four waves' accumulators in a block's LDS)
+constexpr int kStageWords = 192;        // mode indices of a tensor whose hash words a scatter block stages
 constexpr int kMaxLog2Acc = 14;         // sketch words in LDS per scatter block and FFT points in LDS;
                                         // larger m: bucket ranges and the two-pass FFT
 
 struct M1Launch {
-  const ScatterSlot *slots;
+  const ScatterSlot *slots;  // the largest first
   int64_t n_slots;
+  int64_t n_big;             // the slots from n_big on are small (see kSmallSlot)
   const ModeDesc *modes;
   const void *const *data;   // per global tensor
   int dtype;
@@ -102,11 +102,9 @@ struct M1Launch {
   int sb;                    // samples per scatter block
   int banks;                 // accumulator banks per sketch (1: signed adds, 2: sign in the address)
   int log2m;
-  size_t lds_bytes;
   void *ybuf;                // [samples][n_slots][m] (double for F64, float otherwise)
-  // Per-slot power-of-two bound of |x| ([n_slots]; null: every block keeps a
-  // running maximum).  record_bound: this launch is the first to see the
-  // data, its first sample batch records the bounds the others then use.
+  // Per-slot power-of-two bound of |x| ([n_slots]).  record_bound: this launch
+  // is the first to see the data and records the bounds, else it uses them.
   double *slot_bound = nullptr;
   bool record_bound = false;
 };
@@ -152,6 +150,10 @@ int launch_hashgen(const StreamDesc *streams, int64_t n_streams, int64_t W, int6
                    int64_t samples, int64_t m, int64_t max_n, int32_t *out, hipStream_t st);
 
 int launch_m1_scatter(const M1Launch &L, hipStream_t st);
+// LDS of a scatter block: the fixed-point accumulators (`banks` banks of m
+// 8-byte words per sample; 2^kMaxLog2Acc words at most, in bucket ranges), the
+// row words and the block maximum.
+size_t m1_scatter_lds(int sb, int banks, int log2m);
 
 // Network j's tensors are the entries [nets[j].t0, nets[j].t1) of tbeg/tend:
 // entry k's sketch sums the slots [tbeg[k], tend[k]).
