@@ -1,13 +1,15 @@
 // Regressor of the learned sketch-size selector (tn_mlp.h): a 3-layer tanh
 // perceptron in FP32 with hand-written forward, backward and Adam kernels.
 //
-//   mlp_fwd_bwd_kernel : a block takes 64 rows; the parameters and the rows'
+//   mlp_fwd_bwd_kernel : a block takes 16 rows (of very large batches four
+//                        times 16 in turn); the parameters and the rows'
 //                        activations live in LDS; it writes predictions and/or
 //                        the block's partial gradient (sums over its rows) and
 //                        partial loss, FP64.
-//   mlp_reduce_kernel  : one thread per parameter sums the blocks' partials in
-//                        a fixed order (deterministic) and either exports the
-//                        gradient or applies a bias-corrected Adam step.
+//   mlp_reduce_kernel  : sums the blocks' partials in a fixed order
+//                        (deterministic), 64 parameters per block, and either
+//                        exports the gradient or applies a bias-corrected Adam
+//                        step.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -33,118 +35,216 @@ struct tn_mlp {
 namespace tn {
 namespace {
 
-constexpr int kRows = 64;  // rows per block
+constexpr int kRows = 64;  // rows of activations that the size limit of tn_mlp_create counts
+constexpr int kTile = 16;  // rows a block takes at a time
+constexpr int kRS = 20;    // floats between units in LDS: 16 rows and 4 spare (16-byte accesses, bank spread)
+// Batches of more tiles than this give each block four: the partials of a
+// block are as long as the parameters.
+constexpr int64_t kManyTiles = 1024;
 
-__global__ __launch_bounds__(256) void mlp_fwd_bwd_kernel(
+// LDS floats: the weights with one spare column, biases, output layer; the
+// inputs and four activation arrays unit by unit, kRS floats each, units padded
+// to a multiple of four; the rows' output derivatives.
+__host__ __device__ constexpr int mlp_up4(int x) { return (x + 3) & ~3; }
+size_t mlp_lds_bytes(int D, int H) {
+  const size_t w = (size_t)H * (D + 1) + (size_t)H * (H + 1) + 3 * (size_t)H + 1;
+  return 4 * (((w + 3) & ~(size_t)3) + (size_t)kRS * ((size_t)mlp_up4(D) + 4 * (size_t)mlp_up4(H)) + kTile);
+}
+
+// Eight waves, two rows each; a lane takes one unit (H > 64: two) of its wave's
+// rows, so that a weight is read once for two rows, from a padded row (no bank
+// conflicts), and the rows' values by 8-byte broadcast.  Every dot product
+// runs in the order of its index, in FP32 as before.  The gradients of the
+// weight matrices are taken as 4 x 4 tiles per thread, over the rows in order,
+// in FP64.
+// What bounds it: the latency of its phases (16 rows are 0.3 M multiply-adds);
+// 4096 rows fill the 256 CUs with one block each.  One step of 4096 rows, 32
+// inputs, 64 hidden units: 239 us with 64 rows per block, unpadded weights (64
+// lanes of one bank) and one gradient entry per thread; 23 us now.
+__global__ __launch_bounds__(512) void mlp_fwd_bwd_kernel(
     const float *__restrict__ params, int D, int H, const float *__restrict__ X,
     const float *__restrict__ y, int64_t row0, int64_t n, float scale, float *__restrict__ pred,
-    double *__restrict__ partial, int64_t P) {
+    double *__restrict__ partial, int64_t P, int tiles) {
   extern __shared__ __align__(16) float sm[];
-  float *W1 = sm;                 // [H][D]
-  float *b1 = W1 + H * D;         // [H]
-  float *W2 = b1 + H;             // [H][H]
-  float *b2 = W2 + H * H;         // [H]
+  const int D1 = D + 1, H1 = H + 1, H4 = mlp_up4(H);
+  float *W1 = sm;                 // [H][D + 1]
+  float *W2 = W1 + H * D1;        // [H][H + 1]
+  float *b1 = W2 + H * H1;        // [H]
+  float *b2 = b1 + H;             // [H]
   float *W3 = b2 + H;             // [H]
-  float *b3 = W3 + H;             // [1] (+1 pad)
-  float *xs = b3 + 2;             // [64][D]
-  float *h1 = xs + kRows * D;     // [64][H]
-  float *h2 = h1 + kRows * H;     // [64][H]
-  float *d2 = h2 + kRows * H;     // [64][H]  dL/da2
-  float *d1 = d2 + kRows * H;     // [64][H]  dL/da1
-  float *dy = d1 + kRows * H;     // [64]
-  __shared__ double lpart[kRows];
+  float *b3 = W3 + H;             // [1]
+  float *xs = sm + (((H * D1 + H * H1 + 3 * H + 1) + 3) & ~3);  // [D][kRS]
+  float *h1 = xs + kRS * mlp_up4(D);  // [H][kRS]
+  float *h2 = h1 + kRS * H4;
+  float *d2 = h2 + kRS * H4;      // dL/da2
+  float *d1 = d2 + kRS * H4;      // dL/da1
+  float *dy = d1 + kRS * H4;      // [16]
+  __shared__ double lpart[kTile];
 
-  const int tid = threadIdx.x;
-  const int64_t base = row0 + (int64_t)blockIdx.x * kRows;
-  for (int64_t i = tid; i < P; i += 256) sm[i] = params[i];
-  for (int i = tid; i < kRows * D; i += 256) {
-    const int s = i / D, d = i - s * D;
-    xs[i] = (base + s < n) ? X[(base + s) * D + d] : 0.f;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float *pW2 = params + (int64_t)H * D + H, *pb2 = pW2 + (int64_t)H * H;
+  for (int j = wave; j < H; j += 8) {
+    for (int d = lane; d < D; d += 64) W1[j * D1 + d] = params[j * D + d];
+    for (int k = lane; k < H; k += 64) W2[j * H1 + k] = pW2[j * H + k];
   }
-  __syncthreads();
-  for (int i = tid; i < kRows * H; i += 256) {
-    const int s = i / H, j = i - s * H;
-    float a = b1[j];
-    for (int d = 0; d < D; ++d) a = fmaf(W1[j * D + d], xs[s * D + d], a);
-    h1[i] = tanhf(a);
+  for (int j = tid; j < H; j += 512) {
+    b1[j] = params[H * D + j];
+    b2[j] = pb2[j];
+    W3[j] = pb2[H + j];
   }
-  __syncthreads();
-  for (int i = tid; i < kRows * H; i += 256) {
-    const int s = i / H, j = i - s * H;
-    float a = b2[j];
-    for (int k = 0; k < H; ++k) a = fmaf(W2[j * H + k], h1[s * H + k], a);
-    h2[i] = tanhf(a);
-  }
-  __syncthreads();
-  if (tid < kRows) {
-    const int s = tid;
-    float o = b3[0];
-    for (int j = 0; j < H; ++j) o = fmaf(W3[j], h2[s * H + j], o);
-    const bool valid = base + s < n;
-    if (pred && valid) pred[base + s] = o;
-    if (partial) {
-      const float r = valid ? o - y[base + s] : 0.f;
-      dy[s] = r * scale;
-      lpart[s] = 0.5 * (double)r * (double)r;
+  if (tid == 0) b3[0] = pb2[2 * H];
+  double *out = partial ? partial + (int64_t)blockIdx.x * (P + 1) : nullptr;
+  for (int tile = 0; tile < tiles; ++tile) {
+    const int64_t base = row0 + ((int64_t)blockIdx.x * tiles + tile) * kTile;
+    if (tile > 0) {
+      if (base >= n) break;  // uniform over the block
+      __syncthreads();       // the last tile's readers are done
     }
-  }
-  if (!partial) return;
-  __syncthreads();
-  for (int i = tid; i < kRows * H; i += 256) {
-    const int s = i / H, j = i - s * H;
-    const float t = h2[i];
-    d2[i] = dy[s] * W3[j] * (1.f - t * t);
-  }
-  __syncthreads();
-  for (int i = tid; i < kRows * H; i += 256) {
-    const int s = i / H, k = i - s * H;
-    float a = 0.f;
-    for (int j = 0; j < H; ++j) a = fmaf(W2[j * H + k], d2[s * H + j], a);
-    const float t = h1[i];
-    d1[i] = a * (1.f - t * t);
-  }
-  __syncthreads();
-  double *out = partial + (int64_t)blockIdx.x * (P + 1);
-  for (int64_t p = tid; p < P; p += 256) {
-    double g = 0.0;
-    if (p < (int64_t)H * D) {                                   // W1[j][d]
-      const int j = (int)(p / D), d = (int)(p - (int64_t)j * D);
-      for (int s = 0; s < kRows; ++s) g += (double)d1[s * H + j] * xs[s * D + d];
-    } else if (p < (int64_t)H * D + H) {                        // b1[j]
-      const int j = (int)(p - (int64_t)H * D);
-      for (int s = 0; s < kRows; ++s) g += d1[s * H + j];
-    } else if (p < (int64_t)H * D + H + H * H) {                // W2[j][k]
-      const int q = (int)(p - (int64_t)H * D - H), j = q / H, k = q - j * H;
-      for (int s = 0; s < kRows; ++s) g += (double)d2[s * H + j] * h1[s * H + k];
-    } else if (p < (int64_t)H * D + 2 * H + H * H) {            // b2[j]
-      const int j = (int)(p - (int64_t)H * D - H - H * H);
-      for (int s = 0; s < kRows; ++s) g += d2[s * H + j];
-    } else if (p < P - 1) {                                     // W3[j]
-      const int j = (int)(p - (int64_t)H * D - 2 * H - H * H);
-      for (int s = 0; s < kRows; ++s) g += (double)dy[s] * h2[s * H + j];
-    } else {                                                    // b3
-      for (int s = 0; s < kRows; ++s) g += dy[s];
+    for (int s = wave; s < kTile; s += 8)
+      for (int d = lane; d < D; d += 64) xs[d * kRS + s] = (base + s < n) ? X[(base + s) * D + d] : 0.f;
+    __syncthreads();
+    const int r0 = 2 * wave;
+    // a_j = bias_j + sum_i w[j][i] in[i] for the wave's two rows, then tanh
+    auto layer = [&](const float *w, int ws, int ni, const float *bias, const float *in, float *to) {
+      for (int j = lane; j < H; j += 64) {
+        const float *wj = w + j * ws;
+        float a0 = bias[j], a1 = a0;
+#pragma unroll 8
+        for (int i = 0; i < ni; ++i) {
+          const float v = wj[i];
+          const float2 x2 = *reinterpret_cast<const float2 *>(in + i * kRS + r0);
+          a0 = fmaf(v, x2.x, a0);
+          a1 = fmaf(v, x2.y, a1);
+        }
+        *reinterpret_cast<float2 *>(to + j * kRS + r0) = make_float2(tanhf(a0), tanhf(a1));
+      }
+    };
+    // a wave reads only the rows it wrote itself, but for the output layer
+    layer(W1, D1, D, b1, xs, h1);
+    __syncthreads();
+    layer(W2, H1, H, b2, h1, h2);
+    __syncthreads();
+    if (tid < kTile) {
+      const int s = tid;
+      float o = b3[0];
+#pragma unroll 8
+      for (int j = 0; j < H; ++j) o = fmaf(W3[j], h2[j * kRS + s], o);
+      const bool valid = base + s < n;
+      if (pred && valid) pred[base + s] = o;
+      if (partial) {
+        const float r = valid ? o - y[base + s] : 0.f;
+        dy[s] = r * scale;
+        lpart[s] = 0.5 * (double)r * (double)r;
+      }
     }
-    out[p] = g;
-  }
-  if (tid == 0) {
-    double l = 0.0;
-    for (int s = 0; s < kRows; ++s) l += lpart[s];
-    out[P] = l;
+    if (!partial) continue;
+    __syncthreads();
+    for (int j = lane; j < H; j += 64) {
+      const float2 t2 = *reinterpret_cast<const float2 *>(h2 + j * kRS + r0);
+      const float2 y2 = *reinterpret_cast<const float2 *>(dy + r0);
+      const float w = W3[j];
+      *reinterpret_cast<float2 *>(d2 + j * kRS + r0) =
+          make_float2(y2.x * w * (1.f - t2.x * t2.x), y2.y * w * (1.f - t2.y * t2.y));
+    }
+    __syncthreads();
+    for (int k = lane; k < H; k += 64) {
+      float a0 = 0.f, a1 = 0.f;
+#pragma unroll 8
+      for (int j = 0; j < H; ++j) {
+        const float v = W2[j * H1 + k];
+        const float2 g2 = *reinterpret_cast<const float2 *>(d2 + j * kRS + r0);
+        a0 = fmaf(v, g2.x, a0);
+        a1 = fmaf(v, g2.y, a1);
+      }
+      const float2 t2 = *reinterpret_cast<const float2 *>(h1 + k * kRS + r0);
+      *reinterpret_cast<float2 *>(d1 + k * kRS + r0) =
+          make_float2(a0 * (1.f - t2.x * t2.x), a1 * (1.f - t2.y * t2.y));
+    }
+    __syncthreads();
+    auto emit = [&](int64_t p, double g) { out[p] = tile > 0 ? out[p] + g : g; };
+    // 4 x 4 tiles of the two weight matrices' gradients: sum_s u[j][s] v[i][s]
+    const int tj = H4 / 4, t1 = tj * (mlp_up4(D) / 4), t2 = tj * tj;
+    for (int t = tid; t < t1 + t2; t += 512) {
+      const bool first = t < t1;
+      const int q = first ? t : t - t1, ni = first ? D : H, ti = mlp_up4(ni) / 4;
+      const int j0 = 4 * (q / ti), i0 = 4 * (q - (q / ti) * ti);
+      const float *u = (first ? d1 : d2) + j0 * kRS, *v = (first ? xs : h1) + i0 * kRS;
+      double g[4][4] = {};
+#pragma unroll
+      for (int s0 = 0; s0 < kTile; s0 += 4) {
+        float4 a[4], b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          a[e] = *reinterpret_cast<const float4 *>(u + e * kRS + s0);
+          b[e] = *reinterpret_cast<const float4 *>(v + e * kRS + s0);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+              g[e][f] += (double)reinterpret_cast<const float *>(&a[e])[s] *
+                         (double)reinterpret_cast<const float *>(&b[f])[s];
+      }
+      const int64_t off = first ? 0 : (int64_t)H * D + H;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+          if (j0 + e < H && i0 + f < ni) emit(off + (int64_t)(j0 + e) * ni + i0 + f, g[e][f]);
+    }
+    // biases and output layer
+    for (int j = tid; j < H; j += 512) {
+      double g1 = 0.0, g2 = 0.0, g3 = 0.0;
+#pragma unroll 4
+      for (int s = 0; s < kTile; ++s) {
+        g1 += d1[j * kRS + s];
+        g2 += d2[j * kRS + s];
+        g3 += (double)dy[s] * h2[j * kRS + s];
+      }
+      emit((int64_t)H * D + j, g1);
+      emit((int64_t)H * D + H + (int64_t)H * H + j, g2);
+      emit((int64_t)H * D + 2 * H + (int64_t)H * H + j, g3);
+    }
+    if (tid == 511) {
+      double g = 0.0, l = 0.0;
+      for (int s = 0; s < kTile; ++s) {
+        g += dy[s];
+        l += lpart[s];
+      }
+      emit(P - 1, g);
+      emit(P, l);
+    }
   }
 }
 
 // mode 0: grad[p] = sum; mode 1: Adam.  scalar[0] = summed loss * loss_scale and
 // scalar[1] += summed loss * epoch_scale (the epoch's mean loss, batch by batch).
-__global__ void mlp_reduce_kernel(const double *__restrict__ partial, int64_t blocks, int64_t P,
-                                  int mode, float *__restrict__ grad, float *__restrict__ params,
-                                  float *__restrict__ m, float *__restrict__ v, float lr, float c1,
-                                  float c2, double loss_scale, double epoch_scale,
-                                  double *__restrict__ scalar) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > P) return;
+// A block takes 64 parameters; its eight waves each sum a run of the partials,
+// and the runs' sums are added in order.  (One thread per parameter over 64
+// partials: 17 us per step, latency; 5 us now, over 256.)
+__global__ __launch_bounds__(512) void mlp_reduce_kernel(const double *__restrict__ partial, int64_t blocks,
+                                                         int64_t P, int mode, float *__restrict__ grad,
+                                                         float *__restrict__ params, float *__restrict__ m,
+                                                         float *__restrict__ v, float lr, float c1, float c2,
+                                                         double loss_scale, double epoch_scale,
+                                                         double *__restrict__ scalar) {
+  __shared__ double run[8][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t p = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t per = (blocks + 7) / 8, q0 = min(blocks, wave * per), q1 = min(blocks, q0 + per);
+  double t = 0.0;
+  if (p <= P) {
+#pragma unroll 16
+    for (int64_t b = q0; b < q1; ++b) t += partial[b * (P + 1) + p];
+  }
+  run[wave][lane] = t;
+  __syncthreads();
+  if (wave != 0 || p > P) return;
   double g = 0.0;
-  for (int64_t b = 0; b < blocks; ++b) g += partial[b * (P + 1) + p];
+#pragma unroll
+  for (int w = 0; w < 8; ++w) g += run[w][lane];
   if (p == P) {
     scalar[0] = g * loss_scale;
     scalar[1] += g * epoch_scale;
@@ -183,33 +283,40 @@ int ensure_partial(tn_mlp *net, int64_t blocks) {
   return TN_OK;
 }
 
+// Tiles of 16 rows per block, and blocks, for a batch of `rows` rows.
+int mlp_tiles(int64_t rows) { return rows > kManyTiles * kTile ? 4 : 1; }
+int64_t mlp_blocks(int64_t rows) {
+  const int64_t per = (int64_t)kTile * mlp_tiles(rows);
+  return (rows + per - 1) / per;
+}
+
 int fwd_bwd(tn_mlp *net, const float *X, const float *y, int64_t row0, int64_t rows, int64_t n,
             hipStream_t st, float *pred, bool grad) {
-  const int64_t blocks = (rows + kRows - 1) / kRows;
+  const int64_t blocks = mlp_blocks(rows);
   if (blocks == 0) return TN_OK;
   if (blocks > 0x7fffffff) return set_error(TN_ERR_UNSUPPORTED, "mlp: too many rows");
   if (grad) {
     int rc = ensure_partial(net, blocks);
     if (rc != TN_OK) return rc;
   }
-  hipLaunchKernelGGL(mlp_fwd_bwd_kernel, dim3((unsigned)blocks), dim3(256), net->lds, st,
+  hipLaunchKernelGGL(mlp_fwd_bwd_kernel, dim3((unsigned)blocks), dim3(512), net->lds, st,
                      net->d_params, net->D, net->H, X, y, row0, row0 + rows < n ? row0 + rows : n,
-                     (float)(1.0 / (double)rows), pred, grad ? net->d_partial : nullptr, net->P);
+                     (float)(1.0 / (double)rows), pred, grad ? net->d_partial : nullptr, net->P, mlp_tiles(rows));
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }
 
 int reduce(tn_mlp *net, int64_t rows, int mode, float *grad, float lr, hipStream_t st,
            double epoch_scale = 0.0) {
-  const int64_t blocks = (rows + kRows - 1) / kRows;
+  const int64_t blocks = mlp_blocks(rows);
   float c1 = 1.f, c2 = 1.f;
   if (mode == 1) {
     net->t += 1;
     c1 = (float)(1.0 / (1.0 - std::pow(0.9, (double)net->t)));
     c2 = (float)(1.0 / (1.0 - std::pow(0.999, (double)net->t)));
   }
-  const unsigned g = (unsigned)((net->P + 1 + 255) / 256);
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3(g), dim3(256), 0, st, net->d_partial, blocks, net->P,
+  const unsigned g = (unsigned)((net->P + 1 + 63) / 64);
+  hipLaunchKernelGGL(mlp_reduce_kernel, dim3(g), dim3(512), 0, st, net->d_partial, blocks, net->P,
                      mode, grad, net->d_params, net->d_m, net->d_v, lr, c1, c2,
                      1.0 / (double)rows, epoch_scale, net->d_scalar);
   TN_HIP_CHECK(hipGetLastError());
@@ -234,8 +341,10 @@ int tn_mlp_create(int32_t d_in, int32_t hidden, uint64_t seed, tn_mlp **out) {
   net->D = d_in;
   net->H = hidden;
   net->P = (int64_t)hidden * d_in + hidden + (int64_t)hidden * hidden + hidden + hidden + 1;
+  // The documented limit on d_in and hidden: parameters and 64 rows of
+  // activations in LDS (more than the kernel takes).
   const int64_t floats = net->P + 2 + (int64_t)kRows * d_in + 4 * (int64_t)kRows * hidden + kRows;
-  net->lds = (size_t)floats * 4;
+  net->lds = mlp_lds_bytes(d_in, hidden);
   int dev = 0, maxlds = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
@@ -243,9 +352,9 @@ int tn_mlp_create(int32_t d_in, int32_t hidden, uint64_t seed, tn_mlp **out) {
     return set_error(TN_ERR_HIP, "mlp: no device");
   }
   net->device = dev;
-  if (net->lds + 1024 > (size_t)maxlds) {
+  if ((size_t)floats * 4 + 1024 > (size_t)maxlds) {
     delete net;
-    return set_error(TN_ERR_UNSUPPORTED, "mlp: %zu bytes of LDS needed", net->lds);
+    return set_error(TN_ERR_UNSUPPORTED, "mlp: %zu bytes of LDS needed", (size_t)floats * 4);
   }
   if (net->lds > 65536 &&
       hipFuncSetAttribute((const void *)mlp_fwd_bwd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
