@@ -422,11 +422,13 @@ __global__ __launch_bounds__(kTabThreads) void m2_tables_kernel(const M2Node *__
 // qt >= 4 (the column hash then evaluates the higher tensor-sketch levels); the
 // fixed-point scale, the scatter and the gather.  With csplits > 0 the
 // non-leaf child's w is the fixed-order sum of its product's csplits column
-// partials (cpart: [split][tile of the child depth][sample][64], ctiles tiles),
+// partials (cpart: [split][tile of the child depth][sample][kPartRows], ctiles tiles),
 // rounded to A as the partials' sum kernel would store it.
 // A: storage type of w and g (float for FP32/BF16 data, double for FP64).
 constexpr int kWPre = 4, kTPre = 2;
 constexpr int kMaxSplit = 8;  // column ranges per product tile (products below)
+constexpr int kPartRows = 64;  // rows per product tile
+constexpr int kPairSamples = 8;  // most samples a two-child gather block stages
 
 // Byte offset of the gather's w values in its LDS (after the m accumulator
 // words and the tcap slot-table words, 8-byte aligned), and its LDS size.
@@ -439,9 +441,7 @@ constexpr size_t gather_lds(uint32_t m, int tcap) {
   return gather_wv_offset<G>(m, tcap) + (size_t)tcap * 8;
 }
 
-// PAIR: every node of the launch has two children, the second of at most 256
-// values (the two-child loop only: fewer registers, more blocks per CU).
-template <typename T, typename A, typename G, bool PAIR = false>
+template <typename T, typename A, typename G>
 __global__ __launch_bounds__(256) void m2_gather_kernel(
     const M2Node *__restrict__ nodes, const int32_t *__restrict__ level, const void *const *data,
     const int32_t *__restrict__ tables, int64_t W, int64_t sample0, int64_t n_samples, int log2m,
@@ -514,10 +514,11 @@ __global__ __launch_bounds__(256) void m2_gather_kernel(
   auto prefetch = [&](int64_t sp) {
     if (csplits > 0) {  // at most one non-leaf child (planner): its column partials
       if (n_pre > 0 && tid < nd.child_dim[pre_j[0]]) {
-        const int64_t tile = nd.child_tile0[pre_j[0]] + (tid >> 6);
+        const int64_t tile = nd.child_tile0[pre_j[0]] + tid / kPartRows;
 #pragma unroll
         for (int zz = 0; zz < kMaxSplit; ++zz)
-          if (zz < csplits) praw[zz] = cpart[(((int64_t)zz * ctiles + tile) * n_samples + sp) * 64 + (tid & 63)];
+          if (zz < csplits)
+            praw[zz] = cpart[(((int64_t)zz * ctiles + tile) * n_samples + sp) * kPartRows + tid % kPartRows];
       }
     } else {
 #pragma unroll
@@ -606,9 +607,6 @@ __global__ __launch_bounds__(256) void m2_gather_kernel(
     const double inv_sc = ldexp(1.0, -(kAccBits - lgN - e));
 
     G *g = gbuf + s * g_row + nd.g_off;
-    if constexpr (PAIR) {
-      gather_pair<A, G, AW>(nd, tab_base, dtab, wv, acc, mask, sc, inv_sc, g);
-    } else {
     switch (qt) {
       case 1: gather_columns<A, G, 1, AW>(nd, c, tab_base, dtab, wv, acc, tab, coef, mask, m, sc, inv_sc, g); break;
       case 2:
@@ -620,7 +618,6 @@ __global__ __launch_bounds__(256) void m2_gather_kernel(
       case 4: gather_columns<A, G, 4, AW>(nd, c, tab_base, dtab, wv, acc, tab, coef, mask, m, sc, inv_sc, g); break;
       default: gather_columns<A, G, 8, AW>(nd, c, tab_base, dtab, wv, acc, tab, coef, mask, m, sc, inv_sc, g); break;
     }
-    }
     if (r_out && nd.root) {
       for (uint32_t b = tid; b < m; b += 256)
         r_out[s * r_stride + (int64_t)nd.net * m + b] = (double)(std::make_signed_t<AW>)acc[b] * inv_sc;
@@ -628,6 +625,220 @@ __global__ __launch_bounds__(256) void m2_gather_kernel(
     if (tid < kM2MaxChildren) wmax[tid] = wmax_leaf[tid];
     __syncthreads();  // acc, coef, the tables and wmax are rewritten for the next sample
   }
+}
+
+// The same for launches whose nodes all have two children, the second of at most
+// 256 values (bonds and physical legs: tensor trains, binary trees).  Thread t
+// keeps i1 = t mod d1 and walks i0 as in gather_pair.  A block takes `ns`
+// samples: their children's table words and values are staged in LDS first,
+// side by side (a word holds the byte offset of its bucket, its sign in bit 31;
+// a value carries its word's sign), so that the loop over the samples loads
+// nothing from memory, a term of the scatter is one LDS read of its row's
+// pair, an add, an and-or, the fma to fixed point and the LDS atomic, and a
+// column of the gather needs no sign test.  Values are those of gather_pair:
+// bit for bit for FP32 children (their products are exact in FP64), to the
+// fixed-point resolution for FP64 ones (one rounding instead of two).
+// What bounds it: vector instructions and LDS alike (per sample of 64 x 64
+// columns, m = 4096: 64 wave atomics of 9.4 cycles, 64 random reads, the clear;
+// 15 vector instructions per column), the start (two dependent loads, then the
+// staging) and the stores of g.  4096 such samples, FP32: 34.7 us with signs
+// and buckets taken apart per term and the next sample's loads issued inside
+// the loop (where the wait for them is also one for the stores before them),
+// 26 us now.
+// Maximum of non-negative doubles over the wave, in lane 63 (row shifts and row
+// broadcasts: no LDS round trips).
+__device__ __forceinline__ double wave_max(double v) {
+  auto step = [](double x, auto CTRL, auto MASK) {
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return fmax(x, __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, decltype(CTRL)::value, decltype(MASK)::value, 0xf, false),
+                                    __builtin_amdgcn_update_dpp(lo, lo, decltype(CTRL)::value, decltype(MASK)::value, 0xf, false)));
+  };
+  v = step(v, std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});  // row_shr:1
+  v = step(v, std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});  // row_shr:2
+  v = step(v, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});  // row_shr:4
+  v = step(v, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});  // row_shr:8
+  v = step(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});  // row_bcast:15
+  v = step(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});  // row_bcast:31
+  return v;
+}
+
+template <typename A>
+struct PairEntry {  // a child's value, signed, and its table word
+  A x;
+  uint32_t w;
+};
+template <>
+struct __align__(16) PairEntry<double> {
+  double x;
+  uint32_t w, pad;
+};
+
+template <typename T, typename A, typename G>
+__global__ __launch_bounds__(256) void m2_gather_pair_kernel(
+    const M2Node *__restrict__ nodes, const int32_t *__restrict__ level, const void *const *data, int64_t n_samples,
+    int log2m, const uint32_t *__restrict__ ltab, int64_t ltab_off, const A *__restrict__ wbuf, int64_t w_row,
+    G *__restrict__ gbuf, int64_t g_row, double *__restrict__ r_out, int64_t r_stride, int tcap,
+    const double *__restrict__ cpart, int32_t csplits, int32_t ctiles, int32_t ns) {
+  extern __shared__ __align__(16) unsigned char smem[];  // no static LDS: the accumulators start at address 0
+  const M2Node &nd = nodes[level[blockIdx.x]];
+  const uint32_t tid = threadIdx.x, m = 1u << log2m;
+  using AW = std::conditional_t<sizeof(G) == 2, uint32_t, unsigned long long>;
+  using E = PairEntry<A>;
+  constexpr int kAccBits = sizeof(G) == 2 ? 30 : 62;
+  const uint32_t d0 = (uint32_t)nd.child_dim[0], d1 = (uint32_t)nd.child_dim[1], ne = d0 + d1;
+  const uint32_t abytes = ((m * (uint32_t)sizeof(AW)) + 15u) & ~15u;
+  AW *acc = reinterpret_cast<AW *>(smem);                                        // [m]
+  unsigned long long *wmax = reinterpret_cast<unsigned long long *>(smem + abytes);  // [kPairSamples][2]
+  E *ent = reinterpret_cast<E *>(wmax + 2 * kPairSamples);                       // [ns][tcap]
+  const int64_t sA = (int64_t)blockIdx.y * ns;
+  const int nsb = (int)min((int64_t)ns, n_samples - sA);
+  const uint32_t *tab = ltab + ((ltab_off + blockIdx.x) * n_samples + sA) * tcap;
+  const int32_t leaf0 = nd.child_tensor[0], leaf1 = nd.child_tensor[1];
+  // Two samples' loads in flight at a time.
+  for (int s0 = 0; s0 < nsb; s0 += 2) {
+    const int s1 = min(s0 + 1, nsb - 1);
+    for (uint32_t e = tid; e < ne; e += 256) {
+      const bool second = e >= d0;
+      const uint32_t i = second ? e - d0 : e;
+      const int32_t leaf = second ? leaf1 : leaf0;
+      const uint32_t wa = tab[(int64_t)s0 * tcap + e], wb = tab[(int64_t)s1 * tcap + e];
+      A xa, xb;
+      if (leaf >= 0) {
+        xa = xb = (A)load_val<T>(data[leaf], i);
+      } else if (csplits > 0) {  // the partials' sum kernel's order
+        const int64_t tile = (second ? nd.child_tile0[1] : nd.child_tile0[0]) + i / kPartRows;
+        const double *pa = cpart + (tile * n_samples + sA + s0) * kPartRows + i % kPartRows;
+        const int64_t zs = (int64_t)ctiles * n_samples * kPartRows, ds = (int64_t)(s1 - s0) * kPartRows;
+        double a[kMaxSplit], b[kMaxSplit], va = 0.0, vb = 0.0;
+#pragma unroll
+        for (int z = 0; z < kMaxSplit; ++z)
+          if (z < csplits) {
+            a[z] = pa[z * zs];
+            b[z] = pa[z * zs + ds];
+          }
+#pragma unroll
+        for (int z = 0; z < kMaxSplit; ++z)
+          if (z < csplits) {
+            va += a[z];
+            vb += b[z];
+          }
+        xa = (A)va;
+        xb = (A)vb;
+      } else {
+        const A *q = wbuf + (second ? nd.child_w_off[1] : nd.child_w_off[0]) + i;
+        xa = q[(sA + s0) * w_row];
+        xb = q[(sA + s1) * w_row];
+      }
+      auto put = [&](int s, uint32_t w, A x) {
+        E t{};
+        t.x = (w & 0x80000000u) ? -x : x;
+        t.w = ((w & 0x7fffffffu) * (uint32_t)sizeof(AW)) | (w & 0x80000000u);
+        ent[s * tcap + e] = t;
+      };
+      put(s0, wa, xa);
+      put(s1, wb, xb);
+    }
+  }
+  __syncthreads();
+  // max |w| of (sample, child) pairs, a wave each
+  for (int p = tid >> 6; p < 2 * nsb; p += 4) {
+    const uint32_t b0 = (p & 1) ? d0 : 0u, dn = (p & 1) ? d1 : d0;
+    double lm = 0.0;
+    for (uint32_t i = tid & 63; i < dn; i += 64) lm = fmax(lm, fabs((double)ent[(p >> 1) * tcap + b0 + i].x));
+    lm = wave_max(lm);
+    if ((tid & 63) == 63) wmax[p] = (unsigned long long)__double_as_longlong(lm);
+  }
+  const uint32_t R = 256u / d1, i1 = tid % d1, i0s = tid / d1;
+  const bool active = tid < R * d1;
+  const int lgN = max(nd.ncols > 1 ? 64 - __clzll((unsigned long long)(nd.ncols - 1)) : 0, 11);
+  constexpr double kMagic = 6755399441055744.0;
+  const long long kMagicBits = __double_as_longlong(kMagic);
+  // Address of a column's bucket: ((w0 + w1) & amask) | base, one instruction
+  // (the mask in a vector register, the LDS base 0 hidden from the compiler,
+  // which would add it again for every term).
+  uint32_t amask = (m - 1) * (uint32_t)sizeof(AW);
+  asm("" : "+v"(amask));
+  uint32_t base = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char *)smem);
+  asm("" : "+s"(base));
+  using LW = __attribute__((address_space(3))) AW;
+  constexpr int U = 4;
+  for (int s = 0; s < nsb; ++s) {
+    uint4 *a16 = reinterpret_cast<uint4 *>(acc);
+    for (uint32_t i = tid; i < abytes / 16; i += 256) a16[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();  // the accumulators are cleared, the entries staged
+    const double pmax = __longlong_as_double((long long)wmax[2 * s]) * __longlong_as_double((long long)wmax[2 * s + 1]);
+    int e = 0;
+    if (pmax > 0.0) (void)frexp(pmax, &e);
+    const double sc = ldexp(1.0, kAccBits - lgN - e), inv_sc = ldexp(1.0, -(kAccBits - lgN - e));
+    const E *es = ent + s * tcap;
+    const E mine = es[d0 + i1];
+    const double x1 = (double)mine.x * sc;
+    if (active) {
+      auto term = [&](const E &t) {
+        const uint32_t o = ((t.w + mine.w) & amask) | base;
+        __hip_atomic_fetch_add((LW *)o, (AW)(__double_as_longlong(fma((double)t.x, x1, kMagic)) - kMagicBits),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      };
+      uint32_t i0 = i0s;
+      for (; i0 + (U - 1) * R < d0; i0 += U * R) {
+        E t[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) t[u] = es[i0 + u * R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) term(t[u]);
+      }
+      for (; i0 < d0; i0 += R) term(es[i0]);
+    }
+    __syncthreads();
+    G *g = gbuf + (sA + s) * g_row + nd.g_off + i1;
+    if (active) {
+      auto value = [&](AW a, uint32_t w) {
+        double r;
+        if constexpr (sizeof(AW) == 4)
+          r = (double)(int32_t)a * inv_sc;
+        else  // hi 2^32 + lo, rounded once
+          r = fma((double)(int32_t)(a >> 32), 4294967296.0 * inv_sc, (double)(uint32_t)a * inv_sc);
+        if constexpr (sizeof(A) == 4)
+          return __uint_as_float(__float_as_uint((float)r) ^ (w & 0x80000000u));
+        else
+          return __longlong_as_double(__double_as_longlong(r) ^ ((long long)(w & 0x80000000u) << 32));
+      };
+      uint32_t i0 = i0s;
+      for (; i0 + (U - 1) * R < d0; i0 += U * R) {
+        uint32_t w[U];
+        AW a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = es[i0 + u * R].w + mine.w;
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = *(LW *)((w[u] & amask) | base);
+#pragma unroll
+        for (int u = 0; u < U; ++u) store_g(g, (size_t)((i0 + u * R) * d1), value(a[u], w[u]));
+      }
+      for (; i0 < d0; i0 += R) {
+        const uint32_t w = es[i0].w + mine.w;
+        store_g(g, (size_t)(i0 * d1), value(*(LW *)((w & amask) | base), w));
+      }
+    }
+    if (r_out && nd.root)
+      for (uint32_t b = tid; b < m; b += 256)
+        r_out[(sA + s) * r_stride + (int64_t)nd.net * m + b] = (double)(std::make_signed_t<AW>)acc[b] * inv_sc;
+    __syncthreads();  // the accumulators are cleared for the next sample
+  }
+}
+
+// Samples per block of the two-child gather: as many as stage their tables and
+// w beside the accumulators within a quarter of a CU's LDS (four blocks per CU), at
+// most kPairSamples, and few enough for `target` blocks; and its LDS.
+template <typename A, typename G>
+size_t gather_pair_lds(uint32_t m, int tcap, int ns) {
+  return (((size_t)m * (sizeof(G) == 2 ? 4 : 8) + 15) & ~(size_t)15) + 16 * kPairSamples +
+         (size_t)ns * tcap * sizeof(PairEntry<A>);
+}
+template <typename A, typename G>
+int gather_pair_samples(uint32_t m, int tcap, int64_t n, int64_t nodes, int64_t target) {
+  int ns = (int)std::max<int64_t>(1, std::min<int64_t>(kPairSamples, n * nodes / target));
+  while (ns > 1 && gather_pair_lds<A, G>(m, tcap, ns) > 40960) --ns;
+  return ns;
 }
 
 // ---------------------------------------------------------------------------
@@ -700,7 +911,7 @@ struct RawW<uint16_t> {
 // the chunk is summed once.  The 64 x 64 result goes through LDS to coalesced
 // stores: FP64 partials [split][tile][sample][64] when the columns are split,
 // else w or the estimates.
-constexpr int kG16Rows = 64, kG16Samples = 64, kG16Threads = 256, kG16Pad = 17;
+constexpr int kG16Rows = kPartRows, kG16Samples = 64, kG16Threads = 256, kG16Pad = 17;
 constexpr int kProdF64 = 0, kProdBF16 = 1, kProdF32 = 2;  // matrix-core product precision
 
 template <typename T, typename A>
@@ -1011,7 +1222,7 @@ int m2_run_t(tn_plan *p, hipStream_t st, int64_t c0, int64_t n, const int32_t *t
   M2Plan *P = p->m2;
   const size_t lds = gather_lds<G>((uint32_t)p->m, P->tcap);
   auto gk = m2_gather_kernel<T, A, G>;
-  auto gkp = m2_gather_kernel<T, A, G, true>;
+  auto gkp = m2_gather_pair_kernel<T, A, G>;
   constexpr size_t g16 = g16_lds_bytes<T, G>();
   if (g16 > 65536) {
     if constexpr (sizeof(G) == sizeof(A)) {
@@ -1023,12 +1234,11 @@ int m2_run_t(tn_plan *p, hipStream_t st, int64_t c0, int64_t n, const int32_t *t
     TN_HIP_CHECK(hipFuncSetAttribute((const void *)m2_gemm16_kernel<T, A, G, kProdBF16>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)g16));
   }
-  if (lds > 65536) {
-    TN_HIP_CHECK(hipFuncSetAttribute((const void *)gk, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds));
-    TN_HIP_CHECK(hipFuncSetAttribute((const void *)gkp, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds));
-  }
+  if (lds > 65536)
+    TN_HIP_CHECK(hipFuncSetAttribute((const void *)gk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  const size_t lds_pair1 = gather_pair_lds<A, G>((uint32_t)p->m, P->tcap, 1);
+  if (lds_pair1 > 65536)  // (then one sample per block)
+    TN_HIP_CHECK(hipFuncSetAttribute((const void *)gkp, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_pair1));
   if (!P->all_nodes.empty()) {
     hipEvent_t ev = nullptr;
     int rc;
@@ -1047,25 +1257,33 @@ int m2_run_t(tn_plan *p, hipStream_t st, int64_t c0, int64_t n, const int32_t *t
     // the children's depth left its products as column partials: summed here
     const bool cfuse = !export_out && (size_t)d + 1 < P->level_fuse.size() && P->level_fuse[(size_t)d + 1];
     // Every node of the depth with two children, the second of at most 256
-    // values: the two-child kernel (74-80 registers against 116-123).
+    // values: the two-child kernel.
     bool pair = true;
     for (int32_t i : P->level_nodes[(size_t)d]) {
       const M2Node &nd = P->h_nodes[(size_t)i];
       pair = pair && nd.nchild == 2 && nd.child_dim[1] <= 256;
     }
-    // Samples per block: about 1024 blocks per level (four resident per CU;
-    // six for the two-child kernel with BF16 g's 32-bit sketches).
+    // About 1024 blocks per level (four resident per CU).
     const int64_t nn = (int64_t)P->level_nodes[(size_t)d].size();
-    const int64_t target = P->gather_target > 0 ? P->gather_target : (pair && sizeof(G) == 2 ? 1536 : 1024);
-    const int64_t gy = std::max<int64_t>(1, std::min<int64_t>(n, (target + nn - 1) / nn));
-    dim3 g1((unsigned)nn, (unsigned)gy);
-    hipLaunchKernelGGL(pair ? gkp : gk, g1, dim3(256), lds, st, P->d_nodes, P->d_level_nodes[(size_t)d],
-                       (const void *const *)p->d_data, tables, p->W, c0, n, p->log2m, P->d_ltab, P->level_off[(size_t)d],
-                       reinterpret_cast<const A *>(P->d_w), P->w_row,
-                       reinterpret_cast<G *>(P->d_g), P->g_row,
-                       export_out ? P->d_r : nullptr, (int64_t)p->n_nets * p->m, P->tcap,
-                       P->d_part, cfuse ? P->level_splits[(size_t)d + 1] : 0,
-                       cfuse ? (int32_t)P->level_tiles[(size_t)d + 1].size() : 0);
+    const int64_t target = P->gather_target > 0 ? P->gather_target : 1024;
+    const int32_t cz = cfuse ? P->level_splits[(size_t)d + 1] : 0;
+    const int32_t ct = cfuse ? (int32_t)P->level_tiles[(size_t)d + 1].size() : 0;
+    if (pair) {
+      const int ns = gather_pair_samples<A, G>((uint32_t)p->m, P->tcap, n, nn, target);
+      const size_t lp = gather_pair_lds<A, G>((uint32_t)p->m, P->tcap, ns);
+      hipLaunchKernelGGL(gkp, dim3((unsigned)nn, (unsigned)((n + ns - 1) / ns)), dim3(256), lp, st, P->d_nodes,
+                         P->d_level_nodes[(size_t)d], (const void *const *)p->d_data, n, p->log2m, P->d_ltab,
+                         P->level_off[(size_t)d], reinterpret_cast<const A *>(P->d_w), P->w_row,
+                         reinterpret_cast<G *>(P->d_g), P->g_row, export_out ? P->d_r : nullptr,
+                         (int64_t)p->n_nets * p->m, P->tcap, P->d_part, cz, ct, ns);
+    } else {
+      const int64_t gy = std::max<int64_t>(1, std::min<int64_t>(n, (target + nn - 1) / nn));
+      hipLaunchKernelGGL(gk, dim3((unsigned)nn, (unsigned)gy), dim3(256), lds, st, P->d_nodes,
+                         P->d_level_nodes[(size_t)d], (const void *const *)p->d_data, tables, p->W, c0, n, p->log2m,
+                         P->d_ltab, P->level_off[(size_t)d], reinterpret_cast<const A *>(P->d_w), P->w_row,
+                         reinterpret_cast<G *>(P->d_g), P->g_row, export_out ? P->d_r : nullptr,
+                         (int64_t)p->n_nets * p->m, P->tcap, P->d_part, cz, ct);
+    }
     TN_HIP_CHECK(hipGetLastError());
     if ((rc = prof_end(p, st, TN_KERNEL_COMBINE, ev)) != TN_OK) return rc;
     if ((rc = prof_begin(p, st, &ev, TN_KERNEL_SKETCH)) != TN_OK) return rc;
