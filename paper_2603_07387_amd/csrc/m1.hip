@@ -605,8 +605,31 @@ __global__ __launch_bounds__(256) void m1_scatter_small_kernel(
   }
 }
 
+// (pr, pi) *= (qr, qi), its roundings written out: an estimate is the same
+// whichever kernel takes the product.
+__device__ __forceinline__ void times(double &pr, double &pi, double qr, double qi) {
+  const double nr = fma(pr, qr, -(pi * qi));
+  pi = fma(pi, qr, pr * qi);
+  pr = nr;
+}
+
+// The first 256 threads add the terms j0 + t of all NTH threads t, those below
+// H, in the order in which 256 threads would take them: the result does not
+// depend on the block's size.
+template <int NTH>
+__device__ __forceinline__ void sum_as_256(double term, int64_t j0, int64_t H, double *terms, double &sum) {
+  __syncthreads();  // earlier readers are done
+  terms[threadIdx.x] = term;
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    for (int t = threadIdx.x; t < NTH; t += 256)
+      if (j0 + t < H) sum += terms[t];
+  }
+}
+
 // NTH threads: 256, or 1024 for m >= 8192 (a block then fills most of a
-// CU's LDS, and the per-thread share of the half spectrum stays small).
+// CU's LDS, and the per-thread share of the half spectrum stays small) and
+// where there are not more blocks than CUs.
 // The transform is held padded in LDS (pad32).  TWL: the half table of
 // twiddles is staged beside it (padded too); otherwise (no room for it) the
 // two-level table (Tw2) is.
@@ -673,6 +696,35 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
       f2[g] = pk ? y[(int64_t)s2 * M + (b < M ? b : 0)] : (A)0;
     }
   };
+  // Adds the slots [from, to) to a round's points, in slot order, the loads of
+  // U slots in flight together.  (b < M only fails when M < NTH: those threads
+  // read point 0 and store nothing.)
+  constexpr int U = G >= 8 ? 2 : 4;
+  auto add_slots = [&](A *v, int from, int to, int p0) {
+    auto load = [&](A *w, int sl) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int b = p0 + g * NTH + tid;
+        w[g] = y[(int64_t)sl * M + (b < M ? b : 0)];
+      }
+    };
+    int sl = from;
+    for (; sl + U <= to; sl += U) {
+      A w[U][G];
+#pragma unroll
+      for (int i = 0; i < U; ++i) load(w[i], sl + i);
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int g = 0; g < G; ++g) v[g] += w[i][g];
+    }
+    for (; sl < to; ++sl) {
+      A w[G];
+      load(w, sl);
+#pragma unroll
+      for (int g = 0; g < G; ++g) v[g] += w[g];
+    }
+  };
   if constexpr (ONE_ROUND)
     if (kb < ke) first_slots(kb);
 
@@ -685,20 +737,8 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
       A v1[G], v2[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) { v1[g] = f1[g]; v2[g] = f2[g]; }
-      for (int sl = a0 + 1; sl < a1; ++sl) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const int b = g * NTH + tid;
-          v1[g] += y[(int64_t)sl * M + (b < M ? b : 0)];
-        }
-      }
-      for (int sl = b0 + 1; sl < b1; ++sl) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const int b = g * NTH + tid;
-          v2[g] += y[(int64_t)sl * M + (b < M ? b : 0)];
-        }
-      }
+      add_slots(v1, a0 + 1, a1, 0);
+      add_slots(v2, b0 + 1, b1, 0);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const int b = g * NTH + tid;
@@ -709,21 +749,8 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
       A v1[G], v2[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) v1[g] = v2[g] = 0;
-      // (b < M only fails when M < NTH: those threads read point 0 and store nothing)
-      for (int sl = a0; sl < a1; ++sl) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const int b = p0 + g * NTH + tid;
-          v1[g] += y[(int64_t)sl * M + (b < M ? b : 0)];
-        }
-      }
-      for (int sl = b0; sl < b1; ++sl) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const int b = p0 + g * NTH + tid;
-          v2[g] += y[(int64_t)sl * M + (b < M ? b : 0)];
-        }
-      }
+      add_slots(v1, a0, a1, p0);
+      add_slots(v2, b0, b1, p0);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const int b = p0 + g * NTH + tid;
@@ -753,10 +780,7 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
           qr = 0.5 * (ar + br);  // (A + B) / 2
           qi = 0.5 * (ai + bi);
         }
-        const double nr = pr[c] * qr - pi[c] * qi;
-        const double ni = pr[c] * qi + pi[c] * qr;
-        pr[c] = nr;
-        pi[c] = ni;
+        times(pr[c], pi[c], qr, qi);
       }
     }
     __syncthreads();
@@ -772,10 +796,17 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
     return;
   }
   double sum = 0.0;
+  if constexpr (NTH > 256 && LOG2M < 13) {
+    double *terms = reinterpret_cast<double *>(smem);
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int j = tid + NTH * c;
-    if (j < H) sum += ((j == 0 || 2 * j == M) ? 1.0 : 2.0) * pr[c];
+    for (int c = 0; c < NC; ++c)
+      sum_as_256<NTH>((tid + NTH * c == 0 || 2 * (tid + NTH * c) == M ? 1.0 : 2.0) * pr[c], NTH * c, H, terms, sum);
+  } else {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int j = tid + NTH * c;
+      if (j < H) sum += ((j == 0 || 2 * j == M) ? 1.0 : 2.0) * pr[c];
+    }
   }
   const double tot = block_sum<NTH>(sum, red);
   if (tid == 0) est[(int64_t)blockIdx.x * S + sample0 + s] = tot / (double)M;
@@ -783,25 +814,33 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
 
 // The split combine's join: per (network, sample) the product over its
 // gsplit shares' spectra, in share order, then the Hermitian sum as in
-// m1_combine_kernel.
-__global__ __launch_bounds__(256) void m1_combine_join_kernel(const double2 *__restrict__ part, int gsplit,
-                                                              int64_t m, int64_t sample0, int64_t S,
-                                                              double *__restrict__ est) {
-  __shared__ double red[4];
+// m1_combine_kernel.  Its blocks are few, so each is wide and keeps
+// kJoinLoads loads per thread in flight (64 samples of 16 shares, m = 4096:
+// 39 us with 256 threads and one load at a time, 9.2 so).
+constexpr int kJoinThreads = 1024, kJoinLoads = 8;
+__global__ __launch_bounds__(kJoinThreads) void m1_combine_join_kernel(const double2 *__restrict__ part, int gsplit,
+                                                                       int64_t m, int64_t sample0, int64_t S,
+                                                                       double *__restrict__ est) {
+  __shared__ double red[kJoinThreads / 64];
   const int64_t H = m / 2 + 1;
   const double2 *q = part + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * gsplit * H;
+  __shared__ double terms[kJoinThreads];
   double sum = 0.0;
-  for (int64_t j = threadIdx.x; j < H; j += 256) {
+  for (int64_t j0 = 0; j0 < H; j0 += kJoinThreads) {
+    const int64_t j = min(j0 + threadIdx.x, H - 1);
     double pr = 1.0, pi = 0.0;
-    for (int g = 0; g < gsplit; ++g) {
-      const double2 v = q[(int64_t)g * H + j];
-      const double nr = pr * v.x - pi * v.y, ni = pr * v.y + pi * v.x;
-      pr = nr;
-      pi = ni;
+    for (int g0 = 0; g0 < gsplit; g0 += kJoinLoads) {
+      double2 v[kJoinLoads];
+#pragma unroll
+      for (int g = 0; g < kJoinLoads; ++g) v[g] = q[(int64_t)min(g0 + g, gsplit - 1) * H + j];
+#pragma unroll
+      for (int g = 0; g < kJoinLoads; ++g)
+        if (g0 + g < gsplit)
+          times(pr, pi, v[g].x, v[g].y);
     }
-    sum += ((j == 0 || 2 * j == m) ? 1.0 : 2.0) * pr;
+    sum_as_256<kJoinThreads>(((j == 0 || 2 * j == m) ? 1.0 : 2.0) * pr, j0, H, terms, sum);
   }
-  const double tot = block_sum<256>(sum, red);
+  const double tot = block_sum<kJoinThreads>(sum, red);
   if (threadIdx.x == 0) est[(int64_t)blockIdx.x * S + sample0 + blockIdx.y] = tot / (double)m;
 }
 
@@ -1132,7 +1171,8 @@ int scatter_t(const M1Launch &L, hipStream_t st) {
   }
 }
 
-template <typename A, int LOG2M>
+constexpr int64_t kFewCombineBlocks = 256;
+template <typename A, int LOG2M, int NTH = LOG2M >= 13 ? 1024 : 256>
 int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend, const void *ybuf,
               int64_t n_slots, int64_t samples, int64_t sample0, int64_t S, const void *tw,
               double *est, int32_t csplit, double *cpart, hipStream_t st) {
@@ -1146,7 +1186,14 @@ int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
   if constexpr (lds > kMaxLdsBytes) {
     return set_error(TN_ERR_UNSUPPORTED, "combine: the %d-point transform does not fit in LDS", M);
   } else {
-    constexpr int NTH = LOG2M >= 13 ? 1024 : 256;
+    // 1024 threads also where a CU has one block at most (m = 2048, 4096): 32
+    // samples of three tensors of 16 slots each, m = 4096, FP32: 47 us with
+    // 256 threads, 22 so
+    const int64_t blocks = n_nets * samples * csplit;
+    if constexpr (LOG2M >= 11 && NTH == 256)
+      if (blocks <= kFewCombineBlocks)
+        return combine_m<A, LOG2M, 1024>(nets, n_nets, tbeg, tend, ybuf, n_slots, samples, sample0, S, tw, est, csplit,
+                                         cpart, st);
     auto kern = m1_combine_kernel<A, LOG2M, TWL, NTH>;
     if (lds > 65536)
       TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1159,8 +1206,8 @@ int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
                        reinterpret_cast<const A2 *>(tw), est, part);
     TN_HIP_CHECK(hipGetLastError());
     if (split) {
-      hipLaunchKernelGGL(m1_combine_join_kernel, dim3((unsigned)n_nets, (unsigned)samples), dim3(256), 0, st,
-                         part, (int)csplit, (int64_t)M, sample0, S, est);
+      hipLaunchKernelGGL(m1_combine_join_kernel, dim3((unsigned)n_nets, (unsigned)samples),
+                         dim3(kJoinThreads), 0, st, part, (int)csplit, (int64_t)M, sample0, S, est);
       TN_HIP_CHECK(hipGetLastError());
     }
     return TN_OK;
