@@ -636,7 +636,7 @@ __device__ __forceinline__ void sum_as_256(double term, int64_t j0, int64_t H, d
 // Network j's tensors are the entries [nets[j].t0, nets[j].t1) of the slot
 // ranges: entry k's sketch is the sum of the slots [tbeg[k], tend[k]) (a
 // plan's tensors in order: tbeg = first slot of each tensor, tend = tbeg + 1;
-// a partial plan lists each entry's sub-tensors).
+// a partial plan lists each entry's, or each group entry's, sub-tensors).
 template <typename A, int LOG2M, bool TWL, int NTH = 256>
 __global__ __launch_bounds__(NTH) void m1_combine_kernel(
     const NetDesc *__restrict__ nets, const int32_t *__restrict__ tbeg, const int32_t *__restrict__ tend,
@@ -786,7 +786,7 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
     __syncthreads();
   }
 
-  if (part != nullptr) {  // this share's product spectrum, for m1_combine_join_kernel
+  if (part != nullptr) {  // this share's product spectrum, for m1_combine_join_kernel or m1_outer_kernel
     double2 *o = part + (((int64_t)blockIdx.x * gridDim.y + s) * gridDim.z + blockIdx.z) * H;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -842,6 +842,61 @@ __global__ __launch_bounds__(kJoinThreads) void m1_combine_join_kernel(const dou
   }
   const double tot = block_sum<kJoinThreads>(sum, red);
   if (threadIdx.x == 0) est[(int64_t)blockIdx.x * S + sample0 + blockIdx.y] = tot / (double)m;
+}
+
+// All entries of a partial contraction from the product spectra of two groups
+// of its tensor pairs: entry loff[a] + roff[b] of sample s is
+// (1/m) sum_j w_j Re(L_a[j] R_b[j]), L_a = spec[a][s], R_b = spec[nl + b][s],
+// w_j = 1 at j = 0 and m/2, else 2: a real product of depth m + 2, taken on
+// v_mfma_f64_16x16x4f64 (A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
+// D[i][j] element i / 4 of lane j + 16 (i % 4)).  A block owns a 16 x 16 tile
+// of one sample; its waves take the frequencies in turn, four of a row per
+// load instruction (64 bytes), and add their sums in wave order.  Bound by the
+// latency of these loads, which come out of the L2: kOuterLoads of each
+// operand are in flight per lane.
+constexpr int kOuterLoads = 8;
+__global__ __launch_bounds__(256) void m1_outer_kernel(const double2 *__restrict__ spec, int32_t nl, int32_t nr,
+                                                       const int32_t *__restrict__ loff,
+                                                       const int32_t *__restrict__ roff, int64_t m,
+                                                       int64_t sample0, int64_t S, double *__restrict__ est) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  __shared__ double sums[3][64][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int a0 = 16 * (int)blockIdx.x, b0 = 16 * (int)blockIdx.y;
+  const int64_t s = blockIdx.z, n = gridDim.z, H = m / 2 + 1;
+  const double2 *pa = spec + ((int64_t)min(a0 + (lane & 15), nl - 1) * n + s) * H;
+  const double2 *pb = spec + ((int64_t)(nl + min(b0 + (lane & 15), nr - 1)) * n + s) * H;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t j0 = 4 * wave; j0 < H; j0 += 16 * kOuterLoads) {
+    double2 va[kOuterLoads], vb[kOuterLoads];
+#pragma unroll
+    for (int u = 0; u < kOuterLoads; ++u) {
+      const int64_t j = min(j0 + 16 * u + (lane >> 4), H - 1);
+      va[u] = pa[j];
+      vb[u] = pb[j];
+    }
+#pragma unroll
+    for (int u = 0; u < kOuterLoads; ++u) {
+      const int64_t j = j0 + 16 * u + (lane >> 4);
+      const double w = (j == 0 || 2 * j == m) ? 1.0 : 2.0;
+      const bool in = j < H;  // beyond: terms of 0
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? va[u].x : 0.0, in ? w * vb[u].x : 0.0, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? va[u].y : 0.0, in ? -w * vb[u].y : 0.0, acc, 0, 0, 0);
+    }
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sums[wave - 1][lane][i] = acc[i];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  const int b = b0 + (lane & 15);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int a = a0 + 4 * i + (lane >> 4);
+    const double v = ((acc[i] + sums[0][lane][i]) + sums[1][lane][i]) + sums[2][lane][i];
+    if (a < nl && b < nr) est[(int64_t)(loff[a] + roff[b]) * S + sample0 + s] = v / (double)m;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1198,14 +1253,14 @@ int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
     if (lds > 65536)
       TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds));
-    const bool split = csplit > 1 && cpart != nullptr;
+    const bool split = cpart != nullptr;
     dim3 grid((unsigned)n_nets, (unsigned)samples, split ? (unsigned)csplit : 1u);
-    double2 *part = split ? reinterpret_cast<double2 *>(cpart) : nullptr;
+    double2 *part = reinterpret_cast<double2 *>(cpart);
     hipLaunchKernelGGL(kern, grid, dim3(NTH), lds, st, nets, tbeg, tend,
                        reinterpret_cast<const A *>(ybuf), n_slots, sample0, S,
                        reinterpret_cast<const A2 *>(tw), est, part);
     TN_HIP_CHECK(hipGetLastError());
-    if (split) {
+    if (split && est != nullptr) {
       hipLaunchKernelGGL(m1_combine_join_kernel, dim3((unsigned)n_nets, (unsigned)samples),
                          dim3(kJoinThreads), 0, st, part, (int)csplit, (int64_t)M, sample0, S, est);
       TN_HIP_CHECK(hipGetLastError());
@@ -1292,6 +1347,16 @@ int launch_m1_combine(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, 
                              cpart, st);
   return combine_t<float>(nets, n_nets, tbeg, tend, ybuf, n_slots, samples, sample0, S, log2m, tw, est, csplit,
                           cpart, st);
+}
+
+int launch_m1_outer(const double *spec, int64_t nl, int64_t nr, const int32_t *loff, const int32_t *roff,
+                    int64_t samples, int64_t sample0, int64_t S, int64_t m, double *est, hipStream_t st) {
+  if (samples > 65535 || nr > 16 * 65535) return set_error(TN_ERR_UNSUPPORTED, "outer product: grid");
+  const dim3 grid((unsigned)((nl + 15) / 16), (unsigned)((nr + 15) / 16), (unsigned)samples);
+  hipLaunchKernelGGL(m1_outer_kernel, grid, dim3(256), 0, st, reinterpret_cast<const double2 *>(spec), (int32_t)nl,
+                     (int32_t)nr, loff, roff, m, sample0, S, est);
+  TN_HIP_CHECK(hipGetLastError());
+  return TN_OK;
 }
 
 int launch_m1_combine_big(int64_t n_nets, const int32_t *tslot, const int32_t *pairs, const int32_t *pair0,

@@ -130,6 +130,14 @@ struct tn_plan {
   void *d_perm = nullptr;
   int32_t *d_cbeg = nullptr;  // combine: per (entry, tensor) first slot ...
   int32_t *d_cend = nullptr;  // ... and end of slots
+  // Grouped combine: the tensor pairs in two groups, a "network" of d_gnets per
+  // assignment of a group's free modes (d_cbeg, d_cend then list these), whose
+  // product spectra the outer product takes two by two.
+  int64_t group_n[2] = {0, 0};  // assignments of each group (0: every entry on its own)
+  int64_t group_chunk = 0;      // samples that d_gspec holds
+  tn::NetDesc *d_gnets = nullptr;
+  int32_t *d_goff = nullptr;    // [sum of group_n]: each assignment's part of the entry's index
+  double *d_gspec = nullptr;
 
   // acyclic method
   tn::M2Plan *m2 = nullptr;
@@ -182,6 +190,7 @@ int auto_size(const tn_network *nets, int n_nets, int method, uint32_t flags, ui
 int partial_build(tn_plan *p, const tn_network *net);
 int partial_bind(tn_plan *p, const tn_network *nets, hipStream_t st);
 int partial_prepare(tn_plan *p, hipStream_t st);
+int partial_combine(tn_plan *p, int64_t samples, int64_t sample0, double *est, hipStream_t st);
 void partial_release(tn_plan *p);
 int prof_begin(tn_plan *p, hipStream_t st, hipEvent_t *ev, int kind);
 int prof_end(tn_plan *p, hipStream_t st, int kind, hipEvent_t start);

@@ -450,6 +450,8 @@ int m1_run(tn_plan *p, hipStream_t st, double *est) {
       rc = launch_m1_combine_big(p->n_nets, p->d_tslot, p->d_pairs, p->d_pair0, p->n_pairs, p->dtype, p->d_ybuf,
                                  (int64_t)p->h_slots.size(), n, c0, p->S, p->log2m, p->d_tw, p->d_cbuf,
                                  p->d_partial, est, st);
+    else if (p->group_n[0] > 0)
+      rc = partial_combine(p, n, c0, est, st);
     else
       rc = (p->flags & (TN_FLAG_DFT_BF16 | TN_FLAG_DFT_FP8))
                ? launch_m1_combine_dft32(p->d_nets, p->n_nets, p->d_cbeg ? p->d_cbeg : p->d_tslot,

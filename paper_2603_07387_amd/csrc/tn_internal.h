@@ -156,11 +156,18 @@ int launch_m1_scatter(const M1Launch &L, hipStream_t st);
 size_t m1_scatter_lds(int sb, int banks, int log2m);
 
 // Network j's tensors are the entries [nets[j].t0, nets[j].t1) of tbeg/tend:
-// entry k's sketch sums the slots [tbeg[k], tend[k]).
+// entry k's sketch sums the slots [tbeg[k], tend[k]).  With cpart each network
+// and sample takes csplit blocks, whose product spectra over their shares of
+// the pairs, [network][sample][block][m/2 + 1], meet in a join kernel (est
+// null: they stay as they are).
 int launch_m1_combine(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend,
                       int dtype, const void *ybuf, int64_t n_slots, int64_t samples,
                       int64_t sample0, int64_t S, int log2m, const void *twiddles,
                       double *est, int32_t csplit, double *cpart, hipStream_t st);
+// A partial contraction's entries from the spectra of its two groups
+// (spec[nl + nr][samples][m/2 + 1], complex): entry loff[a] + roff[b].
+int launch_m1_outer(const double *spec, int64_t nl, int64_t nr, const int32_t *loff, const int32_t *roff,
+                    int64_t samples, int64_t sample0, int64_t S, int64_t m, double *est, hipStream_t st);
 // The combine with its 1024-point DFTs on the BF16 matrix cores, or with fp8
 // on the FP8 ones (dft.hip; FP32 sketches, m = 1024 only).
 int launch_m1_combine_dft32(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend,
