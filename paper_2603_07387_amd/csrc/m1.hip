@@ -937,6 +937,31 @@ __device__ __forceinline__ A2 twiddle_at(const A2 *__restrict__ tw, uint32_t e, 
   return A2{-t.x, -t.y};
 }
 
+// Two radix-2 stages on four points, as in fft_lds_batch, with the roundings of
+// their complex products written out: the two kernels that take pass 1 give
+// the same bits.
+template <bool SWAP, typename A2>
+__device__ __forceinline__ void big_butterfly(A2 &za, A2 &zb, const A2 w) {
+  const auto tr = fma(w.x, zb.x, -(w.y * zb.y));
+  const auto ti = SWAP ? fma(w.x, zb.y, w.y * zb.x) : fma(w.y, zb.x, w.x * zb.y);
+  zb = A2{za.x - tr, za.y - ti};
+  za = A2{za.x + tr, za.y + ti};
+}
+template <typename A2>
+__device__ __forceinline__ void big_radix4(A2 &z0, A2 &z1, A2 &z2, A2 &z3, const A2 w1, const A2 w2, const A2 w3) {
+  big_butterfly<false>(z0, z1, w1);
+  big_butterfly<false>(z2, z3, w1);
+  big_butterfly<false>(z0, z2, w2);
+  big_butterfly<true>(z1, z3, w3);
+}
+// v w_m^e from the two-level table (likewise).
+template <typename A2>
+__device__ __forceinline__ A2 big_twiddled(const A2 v, const A2 *thi, const A2 *tlo, uint32_t e) {
+  const A2 wh = thi[e / kBigN2], wl = tlo[e % kBigN2];
+  const A2 w = A2{fma(wh.x, wl.x, -(wh.y * wl.y)), fma(wh.y, wl.x, wh.x * wl.y)};
+  return A2{fma(v.x, w.x, -(v.y * w.y)), fma(v.x, w.y, v.y * w.x)};
+}
+
 // Columns per pass-1 block: one 128-byte line of each input row per block
 // for FP32 sketches, 256 bytes for FP64 (the transforms then fill 68 KB of LDS).
 template <typename A>
@@ -994,7 +1019,17 @@ __global__ __launch_bounds__(256) void m1_big_cols_kernel(const int32_t *__restr
     for (int g = 0; g < G; ++g) z[c * kBigStr + pad32(bitrev<8>(r0 + RS * (i0 + g)))] = A2{va[g], vb[g]};
   }
   __syncthreads();
-  fft_lds_batch<A, 8, kBigStr, 256>(z, tw2, CB);  // ends with a barrier
+#pragma unroll 1
+  for (int lg = 1; lg < 8; lg += 2) {
+    const int h = 1 << (lg - 1);
+    for (int q = tid; q < CB * (kBigN2 / 4); q += 256) {
+      A2 *zt = z + (q >> 6) * kBigStr;
+      const int qq = q & 63, k = qq & (h - 1), base = ((qq >> (lg - 1)) << (lg + 1)) + k;
+      big_radix4(zt[pad32(base)], zt[pad32(base + h)], zt[pad32(base + 2 * h)], zt[pad32(base + 3 * h)],
+                 tw2[pad32(k << (8 - lg))], tw2[pad32(k << (7 - lg))], tw2[pad32((k + h) << (7 - lg))]);
+    }
+    __syncthreads();
+  }
   // C[j2][b1] = Z_b1[j2] w_m^(b1 j2): lanes of consecutive b1 write one
   // contiguous run per j2
   A2 *out = cbuf + (s * n_pairs + pr) * (int64_t)m + b1_0 + c;
@@ -1003,9 +1038,299 @@ __global__ __launch_bounds__(256) void m1_big_cols_kernel(const int32_t *__restr
   for (int i = 0; i < RPT; ++i) {
     const int j2 = r0 + RS * i;
     const uint32_t e = (b1 * (uint32_t)j2) & (m - 1);
-    const A2 v = z[c * kBigStr + pad32(j2)], wh = thi[e / kBigN2], wl = tlo[e % kBigN2];
-    const A2 w = A2{wh.x * wl.x - wh.y * wl.y, wh.x * wl.y + wh.y * wl.x};
-    out[(int64_t)j2 * n1] = A2{v.x * w.x - v.y * w.y, v.x * w.y + v.y * w.x};
+    out[(int64_t)j2 * n1] = big_twiddled(z[c * kBigStr + pad32(j2)], thi, tlo, e);
+  }
+}
+
+// Scatter and pass 1 in one kernel, for FP32 sketches of tensors of one slot
+// each: the sketches themselves (m words of each tensor and sample) are neither
+// written nor read.  Block: one tensor pair of one sample; its 32-column
+// ranges of b1 one after the other (`split` blocks share them where the pairs
+// and samples are few).  Per range the 32 x 256 buckets of each tensor are
+// accumulated in LDS in 64-bit fixed point, as in m1_scatter_kernel, and turned
+// into FP32 in registers, 16 points of a column (b2 = q + 16 i) per thread: in
+// bit-reversed order they are one run of 16, so the first four stages of the
+// column's transform stay in the registers.  The points change hands once, in
+// the accumulators' place, and the last four stages leave a thread the results
+// that it stores.
+// The range of a term depends on the low bits of its bucket, row word plus
+// column word: with the tensor's columns sorted by these bits (once per block),
+// a row's terms of one range are consecutive columns, from pos[] of the range's
+// first bits minus the row's, around the end of the (doubled) list.  So a range
+// takes its own terms only, a group of lanes per row.  A column's word holds
+// bucket * 8, sign in bit 31 and, in bits 20 to 29 that the sum of two words'
+// buckets does not reach, the column.
+// 48 lattices of 16 tensors of bond 16 (65536 entries each), 6 samples,
+// m = 65536, FP32: 0.86 ms, against 0.78 for the scatter of the sketches and
+// 0.70 for pass 1 alone.  Bound by vector instructions (974 per thread and
+// range outside the scatter, most of them the transform's) and, in the scatter,
+// by the entries' gather: a load instruction takes a clock per line, and 16
+// lanes of a row fall into 7 of its lines of 1 KB.  Ranges of 64 columns (one
+// block of 1024 threads per CU, half the reads of the entries) take the same
+// time; five terms in flight and 8 lanes to a row 0.92 ms.
+constexpr int kBigCols = 32, kBigThreads = 512;
+constexpr int kBigPos = kBigN2 + kBigCols + 4;  // positions of the n1 low bits, and of the first ones again
+constexpr int kBigTerms = 3;  // loads in flight per lane
+constexpr int64_t kBigSplitBlocks = 256;  // one to a CU
+constexpr int kBigZ = kBigCols * kBigN2;  // buckets of a range: accumulators [b2][column], then points [position][column]
+static_assert(kBigCols * kBigN2 == 16 * kBigThreads, "16 points per thread and range");
+// LDS: transforms, twiddles, and per tensor of the pair the doubled column
+// list, the row words and the columns' positions.
+constexpr size_t big_scatter_lds(int max_cols, int max_rows) {
+  return (size_t)8 * (kBigZ + kBigN2 / 2 + kBigN2 / 64 + 2 * kBigN2) +
+         2 * ((size_t)8 * max_cols + (size_t)4 * max_rows + 4 * kBigPos) + 16;
+}
+// lanes per row (log2) so that kBigTerms rounds take nearly every row's terms
+// of a range: `mean` of them, plus two standard deviations
+__device__ __forceinline__ int big_row_lanes(int mean) {
+  int lg = 2;
+  while (lg < 6 && (kBigTerms << lg) < mean + 2 * (int)sqrtf((float)mean) + 1) ++lg;
+  return lg;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBigThreads, 4) void m1_big_scatter_kernel(
+    const ScatterSlot *__restrict__ slots, const ModeDesc *__restrict__ modes, const void *const *__restrict__ data,
+    const int32_t *__restrict__ tables, int64_t W, const int32_t *__restrict__ pairs, int32_t n_pairs,
+    int32_t samples, int32_t split, int log2m, int max_cols, int max_rows, const float2 *__restrict__ tw,
+    float2 *__restrict__ cbuf, const double *__restrict__ bound_in, double *__restrict__ bound_out) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  // The samples of a pair are neighbours on one XCD (block b runs on XCD b mod
+  // 8): its entries, read once per range, come out of that L2.
+  const int32_t per = samples * split, k8 = (int32_t)(blockIdx.x >> 3);
+  const int32_t pr = k8 / per * 8 + (int32_t)(blockIdx.x & 7);
+  if (pr >= n_pairs) return;  // padding of the grid
+  const int32_t s = k8 % per / split, part = k8 % split;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t m = 1u << log2m, mask = m - 1, n1 = m / kBigN2, lmask = n1 - 1;
+  const int lg1 = log2m - 8;
+  unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem);  // [b2][column of the range]
+  float2 *z = reinterpret_cast<float2 *>(smem);
+  float2 *tw2 = z + kBigZ, *thi = tw2 + kBigN2 / 2 + kBigN2 / 64, *tlo = thi + kBigN2;
+  unsigned long long *s_max = reinterpret_cast<unsigned long long *>(tlo + kBigN2);  // [2]
+  uint32_t *list0 = reinterpret_cast<uint32_t *>(s_max + 2), *rowt0 = list0 + 4 * max_cols;
+  int32_t *pos0 = reinterpret_cast<int32_t *>(rowt0 + 2 * max_rows);
+
+  const int nt = pairs[2 * pr + 1] >= 0 ? 2 : 1;
+  ScatterSlot sl[2];
+  const T __attribute__((address_space(1))) *X[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    sl[t] = slots[pairs[2 * pr + (t < nt ? t : 0)]];
+    X[t] = (const T __attribute__((address_space(1))) *)(reinterpret_cast<const T *>(data[sl[t].tensor]));
+  }
+
+  // Once per block: twiddles, row words, sorted columns, the largest |x|.
+  if (tid < kBigN2 / 2) tw2[pad32(tid)] = tw[(uint32_t)tid * n1];  // w_n2^t = w_m^(t n1)
+  if ((uint32_t)tid < n1) thi[tid] = twiddle_at(tw, (uint32_t)tid * kBigN2, m);
+  if (tid < kBigN2) tlo[tid] = twiddle_at(tw, (uint32_t)tid, m);
+  if (tid < 2) s_max[tid] = 0ull;
+  const int32_t *tab = tables + s * W;
+  // Sum over the modes [u0, u1) of the words of index idx.
+  auto word = [&](int u0, int u1, uint32_t idx) {
+    uint32_t w = 0;
+    for (int u = u1 - 1; u >= u0; --u) {
+      const ModeDesc md = modes[u];
+      const uint32_t qt = u > u0 ? idx / (uint32_t)md.n : 0u, d = idx - qt * (uint32_t)md.n;
+      idx = qt;
+      const uint32_t v = (uint32_t)tab[md.table_off + d];
+      uint32_t h = v & ~kSignBit;
+      if (md.comp) h = (m - h) & mask;
+      w = ((w + (h << 3)) & (mask << 3)) | ((w ^ v) & kSignBit);
+    }
+    return w;
+  };
+  constexpr int CT = kMaxCols / kBigThreads;  // columns per thread
+  uint32_t cw[2][CT];
+  int32_t *cursor = reinterpret_cast<int32_t *>(smem);  // [2][kBigN2], before the accumulators are cleared
+  for (int t = 0; t < nt; ++t)
+    if ((uint32_t)tid < n1) pos0[t * kBigPos + tid] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t >= nt) break;
+    const int mode0 = sl[t].mode0, sp = mode0 + sl[t].split;
+    for (int r = tid; r < sl[t].rows; r += kBigThreads) rowt0[t * max_rows + r] = word(mode0, sp, (uint32_t)r);
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      const int col = tid + i * kBigThreads;
+      if (col >= sl[t].L) continue;
+      cw[t][i] = word(sp, mode0 + sl[t].q, (uint32_t)col);
+      atomicAdd(&pos0[t * kBigPos + ((cw[t][i] >> 3) & lmask)], 1);
+    }
+  }
+  // Largest |x| of each tensor, when it was not recorded before.
+  if (bound_in == nullptr) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (t >= nt) break;
+      using Q = typename Quad<T>::type;
+      const Q __attribute__((address_space(1))) *Xq = (const Q __attribute__((address_space(1))) *)X[t];
+      const uint32_t N = (uint32_t)sl[t].rows * (uint32_t)sl[t].L, NQ = N / 4;
+      float lmax = 0.0f;
+      for (uint32_t i0 = tid; i0 < NQ; i0 += kBigThreads * 8) {
+        Q v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = Xq[min(i0 + (uint32_t)u * kBigThreads, NQ - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) lmax = fmaxf(lmax, fabsf(to_acc_any((T)v[u][i])));
+      }
+      if (4 * NQ + tid < N) lmax = fmaxf(lmax, fabsf(to_acc_any((T)X[t][4 * NQ + tid])));
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) lmax = fmaxf(lmax, __shfl_xor(lmax, off, 64));
+      if (lane == 0) atomicMax(&s_max[t], (unsigned long long)__double_as_longlong((double)lmax));
+    }
+  }
+  __syncthreads();
+  // exclusive sums of the counts, one wave per tensor, four counts to a lane
+  if (tid < 64 * nt) {
+    int32_t *p = pos0 + (tid >> 6) * kBigPos, *c = cursor + (tid >> 6) * kBigN2;
+    const bool in = 4u * (uint32_t)lane < n1;
+    int n[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      n[i] = in ? p[4 * lane + i] : 0;
+      sum += n[i];
+    }
+    int upto = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(upto, off, 64);
+      if (lane >= off) upto += o;
+    }
+    int at = upto - sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (in) p[4 * lane + i] = c[4 * lane + i] = at;
+      at += n[i];
+    }
+    if (lane == 63) p[n1] = upto;
+    // the next turn's first ones
+    const int total = __shfl(upto, 63, 64);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * lane + i <= kBigCols) p[n1 + 4 * lane + i] = total + (upto - sum) + (i > 0 ? n[0] : 0) +
+                                                            (i > 1 ? n[1] : 0) + (i > 2 ? n[2] : 0);
+  }
+  __syncthreads();
+  double sc[2];
+  int scale[2], lgl[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    uint32_t *list = list0 + t * 2 * max_cols;
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      const int col = tid + i * kBigThreads;
+      if (t >= nt || col >= sl[t].L) continue;
+      const int at = atomicAdd(&cursor[t * kBigN2 + ((cw[t][i] >> 3) & lmask)], 1);
+      list[at] = list[at + sl[t].L] = cw[t][i] | ((uint32_t)col << 20);
+    }
+    double bound;
+    if (bound_in != nullptr) {
+      bound = bound_in[sl[t].pad];
+    } else {
+      const double bm = __longlong_as_double((long long)s_max[t < nt ? t : 0]);
+      int e = 0;
+      (void)frexp(bm, &e);  // bm < 2^e
+      bound = bm > 0.0 ? ldexp(1.0, e) : 0.0;
+      if (t < nt && s == 0 && part == 0 && tid == 0) bound_out[sl[t].pad] = bound;
+    }
+    scale[t] = 0;
+    if (bound > 0.0) {
+      const uint32_t N = (uint32_t)sl[t].rows * (uint32_t)sl[t].L;
+      int e;
+      (void)frexp(bound, &e);  // bound = 2^(e - 1)
+      scale[t] = 62 - max(N > 1 ? 32 - __clz(N - 1) : 0, 11) - (e - 1);
+    }
+    sc[t] = ldexp(1.0, scale[t]);
+    lgl[t] = big_row_lanes(max(1, sl[t].L * kBigCols / (int)n1));
+  }
+  __syncthreads();  // the lists are there, the cursors no longer used
+  lds_zero(smem, 8 * kBigCols * kBigN2, tid, kBigThreads);
+
+  constexpr double kMagic = 6755399441055744.0;  // 1.5 2^52: x sc + kMagic holds round(x sc) in its low bits
+  const long long kMagicBits = __double_as_longlong(kMagic);
+  constexpr int kRowBit = 3 + __builtin_ctz(kBigCols);
+  const int sh = lg1 + 3 - kRowBit;  // a word's b2, to its byte offset [b2][kBigCols]
+  const uint32_t lds0 =
+      (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char *)smem);
+  const int c = tid % kBigCols, q0 = tid / kBigCols;
+  const int ranges = (int)n1 / kBigCols;
+  for (int range = part; range < ranges; range += split) {
+    float2 p[16];  // points of column c; at first in the order of their buckets
+    auto sketch = [&](int t, auto put) {
+      const int L = sl[t].L, rows = sl[t].rows, lanes = 1 << lgl[t], sub = tid & (lanes - 1);
+      const uint32_t *list = list0 + t * 2 * max_cols, *rowt = rowt0 + t * max_rows;
+      const int32_t *pos = pos0 + t * kBigPos;
+      for (int r = tid >> lgl[t]; r < rows; r += kBigThreads >> lgl[t]) {
+        const uint32_t h = rowt[r];
+        const uint32_t first = ((uint32_t)(kBigCols * range) - (h >> 3)) & lmask, end = first + kBigCols;
+        const int j0 = pos[first], j1 = pos[end], base = r * L;
+        for (int j = j0 + sub; j < j1; j += kBigTerms * lanes) {
+          uint32_t w[kBigTerms];
+          float x[kBigTerms];
+#pragma unroll
+          for (int k = 0; k < kBigTerms; ++k) w[k] = list[min(j + k * lanes, j1 - 1)];
+#pragma unroll
+          for (int k = 0; k < kBigTerms; ++k) x[k] = to_acc_any(X[t][(uint32_t)base + ((w[k] >> 20) & 1023u)]);
+          // (all loads before the first use: they would sink into the branches)
+#pragma unroll
+          for (int k = 0; k < kBigTerms; ++k) asm volatile("" : "+v"(x[k]));
+#pragma unroll
+          for (int k = 0; k < kBigTerms; ++k) {
+            if (j + k * lanes >= j1) break;
+            const uint32_t a = h + w[k];
+            const double xd = (double)flip_sign(x[k], a & kSignBit);
+            const long long v64 = __double_as_longlong(fma(xd, sc[t], kMagic)) - kMagicBits;
+            const uint32_t at = ((a >> sh) & ((kBigN2 - 1) << kRowBit)) | (a & ((kBigCols - 1) << 3));
+            __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long *)(lds0 + at),
+                                   (unsigned long long)v64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        unsigned long long *a = acc + (q0 + 16 * i) * kBigCols + c;
+        put(i, (float)ldexp((double)(long long)*a, -scale[t]));
+        *a = 0ull;
+      }
+      __syncthreads();
+    };
+    __syncthreads();  // the accumulators are cleared
+    // (bit-reversed: b2 = q0 + 16 i is at 16 bitrev(q0) + bitrev(i))
+    sketch(0, [&](int i, float v) { p[bitrev<4>(i)] = float2{v, 0.0f}; });
+    if (nt == 2) sketch(1, [&](int i, float v) { p[bitrev<4>(i)].y = v; });
+#pragma unroll
+    for (int g = 0; g < 16; g += 4) big_radix4(p[g], p[g + 1], p[g + 2], p[g + 3], tw2[0], tw2[0], tw2[pad32(64)]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      big_radix4(p[k], p[k + 4], p[k + 8], p[k + 12], tw2[pad32(32 * k)], tw2[pad32(16 * k)], tw2[pad32(16 * k + 64)]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[(16 * bitrev<4>(q0) + i) * kBigCols + c] = p[i];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      p[j] = z[(q0 + 16 * j) * kBigCols + c];
+      acc[(q0 + 16 * j) * kBigCols + c] = 0ull;  // nobody else's
+    }
+#pragma unroll
+    for (int g = 0; g < 16; g += 4)
+      big_radix4(p[g], p[g + 1], p[g + 2], p[g + 3], tw2[pad32(8 * q0)], tw2[pad32(4 * q0)], tw2[pad32(4 * q0 + 64)]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int kk = q0 + 16 * k;
+      big_radix4(p[k], p[k + 4], p[k + 8], p[k + 12], tw2[pad32(2 * kk)], tw2[pad32(kk)], tw2[pad32(kk + 64)]);
+    }
+    // C[j2][b1] = Z_b1[j2] w_m^(b1 j2), as in m1_big_cols_kernel
+    const uint32_t b1 = (uint32_t)(range * kBigCols + c);
+    float2 *out = cbuf + ((int64_t)s * n_pairs + pr) * (int64_t)m + b1;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int j2 = q0 + 16 * j;
+      out[(int64_t)j2 * n1] = big_twiddled(p[j], thi, tlo, (b1 * (uint32_t)j2) & mask);
+    }
   }
 }
 
@@ -1275,13 +1600,15 @@ int combine_big(int64_t n_nets, const int32_t *tslot, const int32_t *pairs, cons
                 int log2m, const void *tw, void *cbuf, double *partial, double *est, hipStream_t st) {
   using A2 = typename Cplx<A>::type;
   const uint32_t m = 1u << log2m, n1 = m / kBigN2;
-  constexpr size_t lds = big_cols_lds<A>();
-  TN_HIP_CHECK(hipFuncSetAttribute((const void *)m1_big_cols_kernel<A>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(m1_big_cols_kernel<A>, dim3((unsigned)n_pairs, (unsigned)samples, n1 / big_cols<A>()),
-                     dim3(256), lds, st, tslot, pairs, n_pairs, reinterpret_cast<const A *>(ybuf), n_slots, log2m,
-                     reinterpret_cast<const A2 *>(tw), reinterpret_cast<A2 *>(cbuf));
-  TN_HIP_CHECK(hipGetLastError());
+  if (ybuf != nullptr) {
+    constexpr size_t lds = big_cols_lds<A>();
+    TN_HIP_CHECK(hipFuncSetAttribute((const void *)m1_big_cols_kernel<A>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(m1_big_cols_kernel<A>, dim3((unsigned)n_pairs, (unsigned)samples, n1 / big_cols<A>()),
+                       dim3(256), lds, st, tslot, pairs, n_pairs, reinterpret_cast<const A *>(ybuf), n_slots, log2m,
+                       reinterpret_cast<const A2 *>(tw), reinterpret_cast<A2 *>(cbuf));
+    TN_HIP_CHECK(hipGetLastError());
+  }
   dim3 g2((unsigned)n_nets, (unsigned)samples, kBigRowPairs);
   const A2 *cb = reinterpret_cast<const A2 *>(cbuf), *t2 = reinterpret_cast<const A2 *>(tw);
   if (log2m == 14)
@@ -1334,6 +1661,33 @@ int launch_m1_scatter(const M1Launch &L, hipStream_t st) {
     case TN_BF16: return scatter_t<uint16_t, float>(L, st);
     default: return set_error(TN_ERR_ARG, "scatter: dtype %d", L.dtype);
   }
+}
+
+size_t m1_big_scatter_lds(int max_cols, int max_rows) { return big_scatter_lds(max_cols, max_rows); }
+
+int launch_m1_big_scatter(const M1Launch &L, const int32_t *pairs, int64_t n_pairs, int max_cols, int max_rows,
+                          const void *tw, void *cbuf, hipStream_t st) {
+  if (n_pairs == 0 || L.samples == 0) return TN_OK;
+  // a block per range where whole pairs leave CUs without a block
+  const int64_t ranges = (int64_t)(1 << L.log2m) / kBigN2 / kBigCols, blocks = n_pairs * L.samples;
+  const int64_t split = std::max<int64_t>(1, std::min<int64_t>(ranges, (kBigSplitBlocks + blocks - 1) / blocks));
+  const int64_t grid = (n_pairs + 7) / 8 * 8 * L.samples * split;
+  if (grid > (int64_t)1 << 21 || (L.log2m != 15 && L.log2m != 16))
+    return set_error(TN_ERR_UNSUPPORTED, "scatter with the first transforms: %lld blocks, m = 2^%d", (long long)grid,
+                     L.log2m);
+  const size_t lds = big_scatter_lds(max_cols, max_rows);
+  auto run = [&](auto kern) -> int {
+    TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kBigThreads), lds, st, L.slots, L.modes, L.data, L.tables,
+                       L.W, pairs, (int32_t)n_pairs, (int32_t)L.samples, (int32_t)split, L.log2m, max_cols, max_rows,
+                       reinterpret_cast<const float2 *>(tw), reinterpret_cast<float2 *>(cbuf),
+                       L.record_bound ? nullptr : L.slot_bound, L.slot_bound);
+    TN_HIP_CHECK(hipGetLastError());
+    return TN_OK;
+  };
+  if (L.dtype == TN_F32) return run(m1_big_scatter_kernel<float>);
+  if (L.dtype == TN_BF16) return run(m1_big_scatter_kernel<uint16_t>);
+  return set_error(TN_ERR_ARG, "scatter with the first transforms: dtype %d", L.dtype);
 }
 
 int launch_m1_combine(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend, int dtype,

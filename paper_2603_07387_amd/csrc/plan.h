@@ -75,8 +75,10 @@ struct tn_plan {
   void *d_ybuf = nullptr;
   double *d_slot_bound = nullptr;  // [slots]: power-of-two bound of |x| (see M1Launch)
   bool two_pass = false;        // the m-point FFT does not fit in LDS: two-pass combine
+  bool big_scatter = false;     // its first pass within the scatter
+  int32_t max_cols = 0, max_rows = 0;  // largest slot's, for that
   int64_t n_pairs = 0;          // its tensor pairs (two real sketches per complex transform)
-  int32_t *d_pairs = nullptr;   // [n_pairs][2]: tensors a, b (or -1)
+  int32_t *d_pairs = nullptr;   // [n_pairs][2]: tensors a, b (or -1); with big_scatter places in d_sorted
   int32_t *d_pair0 = nullptr;   // [n_nets + 1]: first pair of each network
   void *d_cbuf = nullptr;       // the two-pass combine's transposed columns
   double *d_partial = nullptr;  // and its per-block row sums

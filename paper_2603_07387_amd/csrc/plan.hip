@@ -286,6 +286,17 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   int rc;
   if ((rc = upload(&p->d_streams, p->h_streams)) != TN_OK) return rc;
   if ((rc = upload(&p->d_modes, p->h_modes)) != TN_OK) return rc;
+  // m >= 2^15, FP32 sketches, every tensor one slot, and its words in the LDS
+  // beside the transforms: the scatter takes the combine's first pass too
+  // (resident plans keep the sketches themselves).
+  if (p->two_pass && p->dtype != TN_F64 && !(p->flags & TN_FLAG_RESIDENT) &&
+      p->h_slots.size() + 1 == p->h_tslot.size()) {
+    for (const ScatterSlot &sl : p->h_slots) {
+      p->max_cols = std::max(p->max_cols, sl.L);
+      p->max_rows = std::max(p->max_rows, sl.rows);
+    }
+    p->big_scatter = m1_big_scatter_lds(p->max_cols, p->max_rows) <= p->max_lds;
+  }
   if (p->fused && (rc = upload(&p->d_slots, p->h_slots)) != TN_OK) return rc;
   // The scatter's order of slots: the largest first, the small ones (one wave
   // per sample: few entries of a tensor of few hash words) last.
@@ -313,13 +324,19 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   p->d_ybuf = yb;
   if ((rc = dev_alloc(&p->d_slot_bound, p->h_slots.size())) != TN_OK) return rc;
   if (p->two_pass) {
-    // the tensors of each network two by two (an odd one out alone)
-    std::vector<int32_t> pairs, pair0;
+    // the tensors of each network two by two (an odd one out alone); with
+    // big_scatter their slots' places in the scatter's order
+    std::vector<int32_t> pairs, pair0, place;
+    if (p->big_scatter) {
+      place.resize(sorted.size());
+      for (size_t i = 0; i < sorted.size(); ++i) place[(size_t)sorted[i].pad] = (int32_t)i;
+    }
+    auto name = [&](int32_t k) { return p->big_scatter ? place[(size_t)k] : k; };
     for (const NetDesc &nd : p->h_nets) {
       pair0.push_back((int32_t)(pairs.size() / 2));
       for (int32_t k = nd.t0; k < nd.t1; k += 2) {
-        pairs.push_back(k);
-        pairs.push_back(k + 1 < nd.t1 ? k + 1 : -1);
+        pairs.push_back(name(k));
+        pairs.push_back(k + 1 < nd.t1 ? name(k + 1) : -1);
       }
     }
     pair0.push_back((int32_t)(pairs.size() / 2));
@@ -443,11 +460,15 @@ int m1_run(tn_plan *p, hipStream_t st, double *est) {
     L.record_bound = c0 == 0;  // the data may have changed since the last call
     hipEvent_t ev = nullptr;
     if ((rc = prof_begin(p, st, &ev, TN_KERNEL_SKETCH)) != TN_OK) return rc;
-    if ((rc = launch_m1_scatter(L, st)) != TN_OK) return rc;
+    rc = p->big_scatter
+             ? launch_m1_big_scatter(L, p->d_pairs, p->n_pairs, p->max_cols, p->max_rows, p->d_tw, p->d_cbuf, st)
+             : launch_m1_scatter(L, st);
+    if (rc != TN_OK) return rc;
     if ((rc = prof_end(p, st, TN_KERNEL_SKETCH, ev)) != TN_OK) return rc;
     if ((rc = prof_begin(p, st, &ev, TN_KERNEL_COMBINE)) != TN_OK) return rc;
     if (p->two_pass)
-      rc = launch_m1_combine_big(p->n_nets, p->d_tslot, p->d_pairs, p->d_pair0, p->n_pairs, p->dtype, p->d_ybuf,
+      rc = launch_m1_combine_big(p->n_nets, p->d_tslot, p->d_pairs, p->d_pair0, p->n_pairs, p->dtype,
+                                 p->big_scatter ? nullptr : p->d_ybuf,
                                  (int64_t)p->h_slots.size(), n, c0, p->S, p->log2m, p->d_tw, p->d_cbuf,
                                  p->d_partial, est, st);
     else if (p->group_n[0] > 0)

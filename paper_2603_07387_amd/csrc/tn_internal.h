@@ -155,6 +155,14 @@ int launch_m1_scatter(const M1Launch &L, hipStream_t st);
 // row words and the block maximum.
 size_t m1_scatter_lds(int sb, int banks, int log2m);
 
+// The scatter and the two-pass combine's first pass in one (FP32 sketches,
+// tensors of one slot each): pairs of L's slots (the second -1 for an odd
+// tensor out), cbuf as for launch_m1_combine_big, which then takes ybuf null.
+// max_cols, max_rows: largest over the slots.
+size_t m1_big_scatter_lds(int max_cols, int max_rows);
+int launch_m1_big_scatter(const M1Launch &L, const int32_t *pairs, int64_t n_pairs, int max_cols, int max_rows,
+                          const void *twiddles, void *cbuf, hipStream_t st);
+
 // Network j's tensors are the entries [nets[j].t0, nets[j].t1) of tbeg/tend:
 // entry k's sketch sums the slots [tbeg[k], tend[k]).  With cpart each network
 // and sample takes csplit blocks, whose product spectra over their shares of
