@@ -1380,7 +1380,11 @@ constexpr int32_t kSplitTargetMax = 2048;
 
 // Column split of the products: a level with few 64 x 64 tiles spreads its
 // columns over up to 8 blocks per tile, towards `target` blocks (512 by
-// default: two per CU), each range still at least 8 chunks of 16 W columns.
+// default: two per CU), each range still at least 2 chunks of 16 W columns (6
+// trains of 9 FP64 cores, bond 27, 500 samples: 260 us per call with at least
+// 8, 225 with 4, 2 or 1; one of 19 cores, bond 31, 182 samples: 515, 353, 296,
+// 270).  With FP32 accumulation, where the ranges are part of the rounding, at
+// least 8.
 // Returns the partials buffer this needs, [splits][tiles][chunk][64] doubles
 // (below target x 2 x 64 x 64 entries: blocks x splits < target).  A split depth
 // d >= 1 is consumed as partials by the gathers of depth d - 1 when each parent
@@ -1390,6 +1394,7 @@ size_t m2_schedule(tn_plan *p, int32_t target) {
   M2Plan *P = p->m2;
   const int64_t chunk = P->chunk;
   const int64_t cc = p->dtype == TN_F64 ? 32 : 64;
+  const int64_t least = p->flags & (TN_FLAG_MFMA_BF16 | TN_FLAG_MFMA_F32) ? 8 : 2;  // chunks to a range
   size_t part = 0;
   P->split_target = target;
   P->level_splits.assign(P->level_tiles.size(), 1);
@@ -1400,7 +1405,7 @@ size_t m2_schedule(tn_plan *p, int32_t target) {
     const int64_t blocks = tiles * ((chunk + kG16Samples - 1) / kG16Samples);
     const int64_t maxc = P->level_maxcols[d];
     int32_t z = 1;
-    while (z < kMaxSplit && blocks * z < target && maxc >= 16 * cc * z) z *= 2;
+    while (z < kMaxSplit && blocks * z < target && maxc >= 2 * least * cc * z) z *= 2;
     const int64_t kc = ((maxc + z - 1) / z + cc - 1) / cc * cc;
     P->level_splits[d] = z;
     P->level_kcols[d] = (int32_t)kc;
