@@ -6,33 +6,20 @@
 namespace tn {
 namespace {
 
-// grid.x: stream, grid.y: sample within the chunk.
-__global__ __launch_bounds__(64) void hashgen_kernel(const StreamDesc *__restrict__ streams,
-                                                     int64_t W, int64_t sample0, uint32_t mask,
-                                                     int32_t *__restrict__ out) {
-  const StreamDesc sd = streams[blockIdx.x];
-  const int64_t r = blockIdx.y;
+// 2^lg lanes per (stream, sample) derive its coefficients, each for itself, and
+// take its indices in turn.  One lane does the least work in all, more take
+// less time each.
+__global__ __launch_bounds__(256) void hashgen_kernel(const StreamDesc *__restrict__ streams, int64_t n_streams,
+                                                      int64_t W, int64_t sample0, int64_t samples, int lg,
+                                                      uint32_t mask, int32_t *__restrict__ out) {
+  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x, pair = gid >> lg, pairs = n_streams * samples;
+  if (pair >= pairs) return;
+  const int64_t r = pairs <= 0xffffffffll ? (int64_t)((uint32_t)pair / (uint32_t)n_streams) : pair / n_streams;
+  const StreamDesc sd = streams[pair - r * n_streams];
   const HashCoeffs c = hash_coeffs(sd.seed, (uint64_t)(sample0 + r), sd.stream);
   int32_t *dst = out + r * W + sd.offset;
-  for (int i = threadIdx.x; i < sd.n; i += 64) dst[i] = (int32_t)hash_packed(c, (uint32_t)i, mask);
-}
-
-// Short streams (every stream of at most kShortStream indices): one thread per
-// (stream, sample) derives the coefficients once and writes the whole stream,
-// instead of a 64-thread block per pair whose lanes all derive the same
-// coefficients for a handful of indices.
-constexpr int kShortStream = 64;
-__global__ __launch_bounds__(256) void hashgen_short_kernel(const StreamDesc *__restrict__ streams,
-                                                            int64_t n_streams, int64_t W, int64_t sample0,
-                                                            int64_t samples, uint32_t mask,
-                                                            int32_t *__restrict__ out) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= n_streams * samples) return;
-  const int64_t r = gid / n_streams, k = gid - r * n_streams;
-  const StreamDesc sd = streams[k];
-  const HashCoeffs c = hash_coeffs(sd.seed, (uint64_t)(sample0 + r), sd.stream);
-  int32_t *dst = out + r * W + sd.offset;
-  for (int i = 0; i < (int)sd.n; ++i) dst[i] = (int32_t)hash_packed(c, (uint32_t)i, mask);
+  const int step = 1 << lg;
+  for (int i = (int)gid & (step - 1); i < sd.n; i += step) dst[i] = (int32_t)hash_packed(c, (uint32_t)i, mask);
 }
 
 __global__ void copy_i32_kernel(const int32_t *__restrict__ src, int32_t *__restrict__ dst,
@@ -51,16 +38,19 @@ int launch_hashgen(const StreamDesc *streams, int64_t n_streams, int64_t W, int6
   if (samples > 65535 || n_streams > 0x7fffffff)
     return set_error(TN_ERR_UNSUPPORTED, "hashgen: %lld samples x %lld streams per launch",
                      (long long)samples, (long long)n_streams);
-  if (max_n <= kShortStream) {
-    const int64_t pairs = n_streams * samples;
-    hipLaunchKernelGGL(hashgen_short_kernel, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, st, streams,
-                       n_streams, W, sample0, samples, (uint32_t)(m - 1), out);
-    TN_HIP_CHECK(hipGetLastError());
-    return TN_OK;
-  }
-  dim3 grid((unsigned)n_streams, (unsigned)samples);
-  hipLaunchKernelGGL(hashgen_kernel, grid, dim3(64), 0, st, streams, W, sample0,
-                     (uint32_t)(m - 1), out);
+  // Lanes until there are 65536 threads (48 pairs of 64 indices: 9.9 us with one
+  // lane each, 3.0 with 64; 6016 pairs of 64: 11.0, 5.0), and up to four while
+  // there are not a million (557056 pairs of 2 to 32: 48 us with one, 31 with
+  // two, 50 with eight; 262144 of 16: 24 with one, 15 with four, 33 with 16).
+  const int64_t pairs = n_streams * samples;
+  int lg = 0;
+  while (lg < 6 && ((int64_t)1 << lg) < max_n && pairs << lg < (lg < 2 ? (int64_t)1 << 20 : (int64_t)1 << 16)) ++lg;
+  const int64_t blocks = ((pairs << lg) + 255) / 256;
+  if (blocks > 0x7fffffff)
+    return set_error(TN_ERR_UNSUPPORTED, "hashgen: %lld samples x %lld streams per launch", (long long)samples,
+                     (long long)n_streams);
+  hipLaunchKernelGGL(hashgen_kernel, dim3((unsigned)blocks), dim3(256), 0, st, streams, n_streams, W, sample0, samples,
+                     lg, (uint32_t)(m - 1), out);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }
