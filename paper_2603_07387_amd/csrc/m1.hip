@@ -323,18 +323,24 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
     }
   };
 
+  // Few rows and columns: the column words too are formed once per block, after
+  // the row words, instead of by every thread for its own columns (64 triangles
+  // of 64 x 64, 256 samples, m = 256, FP64: 205 -> 188 us per call).
+  const bool few = rows + L <= kRowChunk;
   lds_zero(acc, acc_bytes, tid, NT);
   put(grp * gs);
   for (int32_t batch = grp * gs; batch < batch_end; ++batch) {
     const int64_t s0 = (int64_t)batch * SB;
     __syncthreads();  // the staged words are there, the accumulators cleared
     uint32_t lv[SB][4];
+    if (!few) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint32_t w[SB];
-      words((uint32_t)min(c0 + i, L - 1), split, q, s0, w);
+      for (int i = 0; i < 4; ++i) {
+        uint32_t w[SB];
+        words((uint32_t)min(c0 + i, L - 1), split, q, s0, w);
 #pragma unroll
-      for (int s = 0; s < SB; ++s) lv[s][i] = to_offset(w[s]);
+        for (int s = 0; s < SB; ++s) lv[s][i] = to_offset(w[s]);
+      }
     }
     fetch(batch + 1);
     const int nranges = RANGED ? 1 << (log2m - log2acc) : 1;
@@ -344,14 +350,25 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
         const int re = min(rows, rb + kRowChunk);
         if (rb > 0) __syncthreads();  // the last chunk's readers are done
         if (range == 0 || rows > kRowChunk) {
-          for (int r = rb + tid; r < re; r += NT) {
+          // rows, then (few) columns
+          for (int r = rb + tid; r < re + (few ? L : 0); r += NT) {
             uint32_t w[SB];
-            words((uint32_t)(sl.row0 + r), 0, split, s0, w);
+            const bool row = r < re;
+            words(row ? (uint32_t)(sl.row0 + r) : (uint32_t)(r - re), row ? 0 : split, row ? split : q, s0, w);
 #pragma unroll
             for (int s = 0; s < SB; ++s) rowt[(r - rb) * SB + s] = to_offset(w[s]);
           }
         }
         __syncthreads();
+        if (few && range == 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            uint32_t w[SB];
+            load_row<SB>(rowt + (rows + min(c0 + i, L - 1)) * SB, w);
+#pragma unroll
+            for (int s = 0; s < SB; ++s) lv[s][i] = w[s];
+          }
+        }
         if (!active) continue;
         // The thread's rows of this chunk (rt + k RP across chunks, so that nxt
         // runs on).
@@ -1485,6 +1502,7 @@ constexpr size_t kWideLds = 81920;
 // the L2 (256 lattices of bond 16, 32 samples: 2.83 ms per call with 16 samples
 // per block, 2.96 with 32).
 constexpr int64_t kSlotBlocks = 2048, kBlockSamples = 16;
+constexpr int64_t kNarrowSlot = 16384;  // entries
 template <typename T, typename A, int SB, int BANKS, int NT, bool RANGED = false>
 int scatter_launch(const M1Launch &L, hipStream_t st) {
   const int64_t n = L.n_big;
@@ -1519,7 +1537,16 @@ int scatter_sb(const M1Launch &L, hipStream_t st) {
   // CU, so that the CU still runs 16 waves; else 512.
   const bool wide = m1_scatter_lds(SB, L.banks, L.log2m) > kWideLds;
   int rc;
-  if (wide)
+  // 256 threads where every slot is small and there are blocks enough: less of
+  // a batch goes into the words and barriers of a block (64 triangles of 64 x
+  // 64, 256 samples, m = 256: 159 against 188 us per call in FP64, 145 against
+  // 160 in FP32; 96 x 96: 244, 277).  For large slots 512 (256 lattices of
+  // 65536 entries a tensor: 2.81 against 2.89 ms; the ladder 540, 636 us).
+  const int64_t batches = (L.samples + SB - 1) / SB;
+  const bool narrow = L.max_entries <= kNarrowSlot && L.n_big * batches >= kSlotBlocks;
+  if (!wide && narrow)
+    rc = L.banks == 2 ? scatter_launch<T, A, SB, 2, 256>(L, st) : scatter_launch<T, A, SB, 1, 256>(L, st);
+  else if (wide)
     rc = L.banks == 2 ? scatter_launch<T, A, SB, 2, 1024>(L, st) : scatter_launch<T, A, SB, 1, 1024>(L, st);
   else
     rc = L.banks == 2 ? scatter_launch<T, A, SB, 2, 512>(L, st) : scatter_launch<T, A, SB, 1, 512>(L, st);

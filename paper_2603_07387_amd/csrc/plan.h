@@ -69,6 +69,7 @@ struct tn_plan {
   tn::ScatterSlot *d_slots = nullptr;   // (persistent kernel)
   tn::ScatterSlot *d_sorted = nullptr;  // the slots, the largest first
   int64_t n_big = 0;                    // of these, the ones that are not small (they come first)
+  int64_t max_entries = 0;              // of the first of them (the largest slot, if any is not small)
   int32_t *d_tslot = nullptr;
   tn::NetDesc *d_nets = nullptr;
   void *d_tw = nullptr;

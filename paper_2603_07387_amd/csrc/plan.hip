@@ -315,6 +315,7 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     return sx != sy ? sy : (int64_t)x.rows * x.L > (int64_t)y.rows * y.L;
   });
   p->n_big = std::count_if(sorted.begin(), sorted.end(), [&](const ScatterSlot &x) { return !small(x); });
+  if (!sorted.empty()) p->max_entries = (int64_t)sorted[0].rows * sorted[0].L;
   if ((rc = upload(&p->d_sorted, sorted)) != TN_OK) return rc;
   if ((rc = upload(&p->d_tslot, p->h_tslot)) != TN_OK) return rc;
   if ((rc = upload(&p->d_nets, p->h_nets)) != TN_OK) return rc;
@@ -445,6 +446,7 @@ int m1_run(tn_plan *p, hipStream_t st, double *est) {
     M1Launch L{};
     L.slots = p->d_sorted;
     L.n_big = p->n_big;
+    L.max_entries = p->max_entries;
     L.n_slots = (int64_t)p->h_slots.size();
     L.modes = p->d_modes;
     L.data = p->d_data;
@@ -591,6 +593,7 @@ int m1_autotune(tn_plan *p, hipStream_t st) {
             M1Launch L{};
             L.slots = p->d_sorted;
             L.n_big = p->n_big;
+            L.max_entries = p->max_entries;
             L.n_slots = (int64_t)p->h_slots.size();
             L.modes = p->d_modes;
             L.data = p->d_data;
@@ -1027,6 +1030,7 @@ int plan_get_sketches(tn_plan *p, const tn_network *nets, int64_t first, int64_t
     M1Launch L{};
     L.slots = p->d_sorted;
     L.n_big = p->n_big;
+    L.max_entries = p->max_entries;
     L.n_slots = (int64_t)p->h_slots.size();
     L.modes = p->d_modes;
     L.data = p->d_data;

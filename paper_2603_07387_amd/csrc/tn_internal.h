@@ -93,6 +93,7 @@ struct M1Launch {
   const ScatterSlot *slots;  // the largest first
   int64_t n_slots;
   int64_t n_big;             // the slots from n_big on are small (see kSmallSlot)
+  int64_t max_entries;       // entries of the largest slot
   const ModeDesc *modes;
   const void *const *data;   // per global tensor
   int dtype;
