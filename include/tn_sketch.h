@@ -210,7 +210,7 @@ typedef struct tn_plan tn_plan;
  *                  and synchronize the default stream.  tn_plan_query keys 3
  *                  and 2 return the chosen m and S.  Otherwise m is
  *                  1 <= m <= 65536 for TN_CYCLIC (above 16384 the scatter
- *                  splits each sketch's buckets over blocks and takes one
+ *                  takes each sketch's buckets in ranges and one
  *                  sample per pass; when the m-point FFT does not fit in LDS,
  *                  from 16384 with TN_F64 data and 32768 otherwise, the combine
  *                  runs in two passes through a device workspace of
