@@ -893,6 +893,7 @@ int contract_exact(const tn_network *net, hipStream_t st, double *out) {
       std::vector<double> memo(trees[(size_t)c].left.size(), -1.0);
       DTensor r;
       if ((rc = run_tree(dry, trees[(size_t)c], trees[(size_t)c].root, ts, &memo, &r)) != TN_OK) return rc;
+      dry.release(&r);  // as the run does: from here on the two layouts must stay the same
     }
     log_msg(1, "exact: %d tensors in %d components, peak %.3g GB of device memory (%.3g GB free)", p, n_comp,
             (double)dry.peak / 1e9, (double)free_b / 1e9);
