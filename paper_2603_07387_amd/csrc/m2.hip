@@ -772,12 +772,16 @@ __global__ __launch_bounds__(256) void m2_gather_pair_kernel(
     const double sc = ldexp(1.0, kAccBits - lgN - e), inv_sc = ldexp(1.0, -(kAccBits - lgN - e));
     const E *es = ent + s * tcap;
     const E mine = es[d0 + i1];
-    const double x1 = (double)mine.x * sc;
-    if (active) {
+    // The scale goes to the second child's value, once per sample, unless that
+    // overflows (FP64 first children below 2^-972): then to the product.
+    const bool fold = sizeof(A) == 4 || sc * __longlong_as_double((long long)wmax[2 * s + 1]) < INFINITY;
+    const double x1 = fold ? (double)mine.x * sc : (double)mine.x;
+    auto scatter = [&](auto FOLD) {
       auto term = [&](const E &t) {
         const uint32_t o = ((t.w + mine.w) & amask) | base;
-        __hip_atomic_fetch_add((LW *)o, (AW)(__double_as_longlong(fma((double)t.x, x1, kMagic)) - kMagicBits),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const double v = decltype(FOLD)::value ? fma((double)t.x, x1, kMagic) : fma((double)t.x * x1, sc, kMagic);
+        __hip_atomic_fetch_add((LW *)o, (AW)(__double_as_longlong(v) - kMagicBits), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
       };
       uint32_t i0 = i0s;
       for (; i0 + (U - 1) * R < d0; i0 += U * R) {
@@ -788,6 +792,12 @@ __global__ __launch_bounds__(256) void m2_gather_pair_kernel(
         for (int u = 0; u < U; ++u) term(t[u]);
       }
       for (; i0 < d0; i0 += R) term(es[i0]);
+    };
+    if (active) {
+      if (fold)  // uniform over the block
+        scatter(std::true_type{});
+      else if constexpr (sizeof(A) == 8)
+        scatter(std::false_type{});
     }
     __syncthreads();
     G *g = gbuf + (sA + s) * g_row + nd.g_off + i1;
