@@ -100,7 +100,7 @@ __device__ __forceinline__ void load_row(const uint32_t *p, uint32_t *out) {
 //
 // The fixed-point scale is 62 - lgN - e for |x| < 2^e and N <= 2^lgN terms, so
 // sums cannot overflow and do not depend on the order of the atomics.  bound_in:
-// per slot the power of two 2^e (0 for an all-zero slot) recorded before;
+// per slot the power of two 2^(e - 1) (0 for an all-zero slot) recorded before;
 // without it the block first takes the maximum over its slot (read again by
 // the scatter, from the caches); the first group's blocks record it in
 // bound_out.
@@ -245,8 +245,8 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
     __syncthreads();
     const double bm = __longlong_as_double((long long)s_max[0]);
     int e = 0;
-    (void)frexp(bm, &e);  // bm < 2^e
-    bound = bm > 0.0 ? ldexp(1.0, e) : 0.0;
+    (void)frexp(bm, &e);  // 2^(e - 1) <= bm < 2^e
+    bound = bm > 0.0 ? ldexp(1.0, e - 1) : 0.0;
     if (bound_out != nullptr && tid == 0 && grp == 0) bound_out[sid] = bound;
   }
   int scale = 0;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
     const uint32_t N = (uint32_t)rows * (uint32_t)L;
     int e;
     (void)frexp(bound, &e);  // bound = 2^(e - 1)
-    scale = 62 - max(N > 1 ? 32 - __clz(N - 1) : 0, 11) - (e - 1);
+    scale = 62 - max(N > 1 ? 32 - __clz(N - 1) : 0, 11) - e;
   }
   const double sc = ldexp(1.0, scale);
   double scq[4];  // 0 for columns past the row or covered by the vector before
@@ -1249,8 +1249,8 @@ __global__ __launch_bounds__(kBigThreads, 4) void m1_big_scatter_kernel(
     } else {
       const double bm = __longlong_as_double((long long)s_max[t < nt ? t : 0]);
       int e = 0;
-      (void)frexp(bm, &e);  // bm < 2^e
-      bound = bm > 0.0 ? ldexp(1.0, e) : 0.0;
+      (void)frexp(bm, &e);  // 2^(e - 1) <= bm < 2^e
+      bound = bm > 0.0 ? ldexp(1.0, e - 1) : 0.0;
       if (t < nt && s == 0 && part == 0 && tid == 0) bound_out[sl[t].pad] = bound;
     }
     scale[t] = 0;
@@ -1258,7 +1258,7 @@ __global__ __launch_bounds__(kBigThreads, 4) void m1_big_scatter_kernel(
       const uint32_t N = (uint32_t)sl[t].rows * (uint32_t)sl[t].L;
       int e;
       (void)frexp(bound, &e);  // bound = 2^(e - 1)
-      scale[t] = 62 - max(N > 1 ? 32 - __clz(N - 1) : 0, 11) - (e - 1);
+      scale[t] = 62 - max(N > 1 ? 32 - __clz(N - 1) : 0, 11) - e;
     }
     sc[t] = ldexp(1.0, scale[t]);
     lgl[t] = big_row_lanes(max(1, sl[t].L * kBigCols / (int)n1));

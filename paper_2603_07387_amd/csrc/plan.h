@@ -74,7 +74,7 @@ struct tn_plan {
   tn::NetDesc *d_nets = nullptr;
   void *d_tw = nullptr;
   void *d_ybuf = nullptr;
-  double *d_slot_bound = nullptr;  // [slots]: power-of-two bound of |x| (see M1Launch)
+  double *d_slot_bound = nullptr;  // [slots]: power of two below the largest |x| (see M1Launch)
   bool two_pass = false;        // the m-point FFT does not fit in LDS: two-pass combine
   bool big_scatter = false;     // its first pass within the scatter
   int32_t max_cols = 0, max_rows = 0;  // largest slot's, for that

@@ -104,7 +104,7 @@ struct M1Launch {
   int banks;                 // accumulator banks per sketch (1: signed adds, 2: sign in the address)
   int log2m;
   void *ybuf;                // [samples][n_slots][m] (double for F64, float otherwise)
-  // Per-slot power-of-two bound of |x| ([n_slots]).  record_bound: this launch
+  // Per slot the largest power of two up to its largest |x| ([n_slots]; 0: all zero).  record_bound: this launch
   // is the first to see the data and records the bounds, else it uses them.
   double *slot_bound = nullptr;
   bool record_bound = false;
