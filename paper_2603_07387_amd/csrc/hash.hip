@@ -8,17 +8,20 @@ namespace {
 
 // 2^lg lanes per (stream, sample) derive its coefficients, each for itself, and
 // take its indices in turn.  One lane does the least work in all, more take
-// less time each.
+// less time each.  WAVE: 64 lanes, so that the pair is the wave's and its
+// coefficients are derived in scalar registers.
+template <bool WAVE>
 __global__ __launch_bounds__(256) void hashgen_kernel(const StreamDesc *__restrict__ streams, int64_t n_streams,
                                                       int64_t W, int64_t sample0, int64_t samples, int lg,
                                                       uint32_t mask, int32_t *__restrict__ out) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x, pair = gid >> lg, pairs = n_streams * samples;
+  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x, pairs = n_streams * samples;
+  const int64_t pair = WAVE ? (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : gid >> lg;
   if (pair >= pairs) return;
   const int64_t r = pairs <= 0xffffffffll ? (int64_t)((uint32_t)pair / (uint32_t)n_streams) : pair / n_streams;
   const StreamDesc sd = streams[pair - r * n_streams];
   const HashCoeffs c = hash_coeffs(sd.seed, (uint64_t)(sample0 + r), sd.stream);
   int32_t *dst = out + r * W + sd.offset;
-  const int step = 1 << lg;
+  const int step = WAVE ? 64 : 1 << lg;
   for (int i = (int)gid & (step - 1); i < sd.n; i += step) dst[i] = (int32_t)hash_packed(c, (uint32_t)i, mask);
 }
 
@@ -42,14 +45,22 @@ int launch_hashgen(const StreamDesc *streams, int64_t n_streams, int64_t W, int6
   // lane each, 3.0 with 64; 6016 pairs of 64: 11.0, 5.0), and up to four while
   // there are not a million (557056 pairs of 2 to 32: 48 us with one, 31 with
   // two, 50 with eight; 262144 of 16: 24 with one, 15 with four, 33 with 16).
+  // Streams of more than 64 indices: enough lanes for 64 each (16384 pairs of
+  // 512: 17.8 us with 64 lanes, 18.8 with four, 17.0 with eight), above 512 all
+  // 64, whose stores are whole lines (16500 pairs of 1024: 16.2 us with 64 lanes,
+  // 25.6 with four, 17.4 with 16).
+  constexpr int64_t kLaneIndices = 64, kLongStream = 512;
   const int64_t pairs = n_streams * samples;
   int lg = 0;
-  while (lg < 6 && ((int64_t)1 << lg) < max_n && pairs << lg < (lg < 2 ? (int64_t)1 << 20 : (int64_t)1 << 16)) ++lg;
+  while (lg < 6 && ((int64_t)1 << lg) < max_n &&
+         (pairs << lg < (lg < 2 ? (int64_t)1 << 20 : (int64_t)1 << 16) ||
+          max_n >> lg > kLaneIndices || max_n > kLongStream))
+    ++lg;
   const int64_t blocks = ((pairs << lg) + 255) / 256;
   if (blocks > 0x7fffffff)
     return set_error(TN_ERR_UNSUPPORTED, "hashgen: %lld samples x %lld streams per launch", (long long)samples,
                      (long long)n_streams);
-  hipLaunchKernelGGL(hashgen_kernel, dim3((unsigned)blocks), dim3(256), 0, st, streams, n_streams, W, sample0, samples,
+  hipLaunchKernelGGL(lg == 6 ? hashgen_kernel<true> : hashgen_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, streams, n_streams, W, sample0, samples,
                      lg, (uint32_t)(m - 1), out);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
