@@ -20,6 +20,7 @@
 //   sample_stats: FP64 mean and unbiased variance over samples per network.
 #include <algorithm>
 
+#include "block_map.h"
 #include "m1_device.h"
 
 #include <hip/hip_bf16.h>
@@ -110,8 +111,7 @@ __device__ __forceinline__ void load_row(const uint32_t *p, uint32_t *out) {
 // outside the current one.
 //
 // slots: in decreasing order of size (pad: the slot's number), so that the last
-// blocks to start are short.  The groups of the same 8 slots are neighbours:
-// block b runs on XCD b mod 8, so a slot's groups share an L2.
+// blocks to start are short; their blocks as slot_block gives them.
 // Registers: six waves per SIMD (three blocks per CU) for 512-thread blocks with
 // one bank, whose LDS leaves room for them at m = 1024 (batch of 4096 networks:
 // 2.64 against 2.75 ms per call with four, and with four row vectors in flight
@@ -128,9 +128,8 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
   static_assert(kStageWords <= NT, "one staged word per thread");
   // No static LDS: the accumulators start at LDS address 0.
   extern __shared__ __align__(16) unsigned char smem[];
-  const uint32_t blk = blockIdx.x / (8u * (uint32_t)gx), rem = blockIdx.x - blk * 8u * (uint32_t)gx;
-  const int32_t pos = (int32_t)(blk * 8u + (rem & 7u));
-  const int32_t grp = (int32_t)(rem >> 3) + (int32_t)blockIdx.y * gx;
+  const SlotBlock sb = slot_block(blockIdx.x, (uint32_t)n, (uint32_t)gx);
+  const int32_t pos = (int32_t)sb.slot, grp = (int32_t)sb.group + (int32_t)blockIdx.y * gx;
   if (pos >= n || grp >= groups) return;  // padding of the grid
   const ScatterSlot sl = slots[pos];
   const int32_t sid = sl.pad;
@@ -487,9 +486,8 @@ __global__ __launch_bounds__(256) void m1_scatter_small_kernel(
   constexpr int K = kSmallSlot / 64, KW = kStageWords / 64;
   static_assert(kStageWords <= 255 && kStageWords % 64 == 0, "word positions are packed in bytes");
   extern __shared__ __align__(16) unsigned char smem[];
-  const uint32_t blk = blockIdx.x / (8u * (uint32_t)gx), rem = blockIdx.x - blk * 8u * (uint32_t)gx;
-  const int32_t pos = (int32_t)(blk * 8u + (rem & 7u));
-  const int32_t grp = (int32_t)(rem >> 3) + (int32_t)blockIdx.y * gx;
+  const SlotBlock sb = slot_block(blockIdx.x, (uint32_t)n, (uint32_t)gx);
+  const int32_t pos = (int32_t)sb.slot, grp = (int32_t)sb.group + (int32_t)blockIdx.y * gx;
   if (pos >= n || grp >= groups) return;  // padding of the grid
   const ScatterSlot sl = slots[pos];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1112,12 +1110,11 @@ __global__ __launch_bounds__(kBigThreads, 4) void m1_big_scatter_kernel(
     int32_t samples, int32_t split, int log2m, int max_cols, int max_rows, const float2 *__restrict__ tw,
     float2 *__restrict__ cbuf, const double *__restrict__ bound_in, double *__restrict__ bound_out) {
   extern __shared__ __align__(16) unsigned char smem[];
-  // The samples of a pair are neighbours on one XCD (block b runs on XCD b mod
-  // 8): its entries, read once per range, come out of that L2.
-  const int32_t per = samples * split, k8 = (int32_t)(blockIdx.x >> 3);
-  const int32_t pr = k8 / per * 8 + (int32_t)(blockIdx.x & 7);
+  // (slot_block: the samples of a pair are neighbours on one XCD; its entries,
+  // read once per range, come out of that L2)
+  const SlotBlock sb = slot_block(blockIdx.x, (uint32_t)n_pairs, (uint32_t)(samples * split));
+  const int32_t pr = (int32_t)sb.slot, s = (int32_t)sb.group / split, part = (int32_t)sb.group % split;
   if (pr >= n_pairs) return;  // padding of the grid
-  const int32_t s = k8 % per / split, part = k8 % split;
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t m = 1u << log2m, mask = m - 1, n1 = m / kBigN2, lmask = n1 - 1;
   const int lg1 = log2m - 8;
@@ -1517,7 +1514,7 @@ int scatter_launch(const M1Launch &L, hipStream_t st) {
   // groups per grid row: the grid's x extent stays within 2^31 threads
   const int64_t slots8 = (n + 7) / 8 * 8;
   const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(groups, ((int64_t)1 << 21) / slots8));
-  const dim3 grid((unsigned)(slots8 * gx), (unsigned)((groups + gx - 1) / gx));
+  const dim3 grid(slot_blocks((uint32_t)n, (uint32_t)gx), (unsigned)((groups + gx - 1) / gx));
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, L.slots, (int32_t)n, L.modes, L.data, L.tables, L.W,
                      L.samples, L.log2m, L.n_slots, reinterpret_cast<A *>(L.ybuf),
                      L.record_bound ? nullptr : L.slot_bound, L.slot_bound, (int32_t)gs, (int32_t)groups,
@@ -1560,9 +1557,10 @@ int scatter_sb(const M1Launch &L, hipStream_t st) {
   auto kern = m1_scatter_small_kernel<T, A>;
   if (lds > 65536)
     TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(kern, dim3((unsigned)(slots8 * gx), (unsigned)((groups + gx - 1) / gx)), dim3(256), lds, st,
-                     L.slots + L.n_big, (int32_t)n, L.modes, L.data, L.tables, L.W, L.samples, L.log2m, L.n_slots,
-                     reinterpret_cast<A *>(L.ybuf), (int32_t)gs, (int32_t)groups, (int32_t)gx);
+  const dim3 grid(slot_blocks((uint32_t)n, (uint32_t)gx), (unsigned)((groups + gx - 1) / gx));
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, L.slots + L.n_big, (int32_t)n, L.modes, L.data, L.tables, L.W,
+                     L.samples, L.log2m, L.n_slots, reinterpret_cast<A *>(L.ybuf), (int32_t)gs,
+                     (int32_t)groups, (int32_t)gx);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }
@@ -1698,7 +1696,7 @@ int launch_m1_big_scatter(const M1Launch &L, const int32_t *pairs, int64_t n_pai
   // a block per range where whole pairs leave CUs without a block
   const int64_t ranges = (int64_t)(1 << L.log2m) / kBigN2 / kBigCols, blocks = n_pairs * L.samples;
   const int64_t split = std::max<int64_t>(1, std::min<int64_t>(ranges, (kBigSplitBlocks + blocks - 1) / blocks));
-  const int64_t grid = (n_pairs + 7) / 8 * 8 * L.samples * split;
+  const int64_t grid = (n_pairs * L.samples * split + kXcds - 1) / kXcds * kXcds;
   if (grid > (int64_t)1 << 21 || (L.log2m != 15 && L.log2m != 16))
     return set_error(TN_ERR_UNSUPPORTED, "scatter with the first transforms: %lld blocks, m = 2^%d", (long long)grid,
                      L.log2m);
