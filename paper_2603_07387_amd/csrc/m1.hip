@@ -108,7 +108,8 @@ __device__ __forceinline__ void load_row(const uint32_t *p, uint32_t *out) {
 //
 // RANGED (m above 2^kMaxLog2Acc buckets, one bank, one sample): the block takes
 // the ranges of 2^kMaxLog2Acc buckets one after the other and drops the terms
-// outside the current one.
+// outside the current one; `rsplit` blocks share a group's ranges where the
+// groups are few.
 //
 // slots: in decreasing order of size (pad: the slot's number), so that the last
 // blocks to start are short; their blocks as slot_block gives them.
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
     const ScatterSlot *__restrict__ slots, int32_t n, const ModeDesc *__restrict__ modes,
     const void *const *__restrict__ data, const int32_t *__restrict__ tables, int64_t W, int64_t samples,
     int log2m, int64_t n_slots, A *__restrict__ ybuf, const double *__restrict__ bound_in,
-    double *__restrict__ bound_out, int32_t gs, int32_t groups, int32_t gx) {
+    double *__restrict__ bound_out, int32_t gs, int32_t groups, int32_t gx, int32_t rsplit) {
   static_assert(!RANGED || (BANKS == 1 && SB == 1), "bucket ranges use one bank and one sample");
   using Q = typename Quad<T>::type;
   constexpr int U = BANKS == 1 || SB * sizeof(T) >= 32 ? 2 : 4;  // row vectors in flight per thread
@@ -129,7 +130,8 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
   // No static LDS: the accumulators start at LDS address 0.
   extern __shared__ __align__(16) unsigned char smem[];
   const SlotBlock sb = slot_block(blockIdx.x, (uint32_t)n, (uint32_t)gx);
-  const int32_t pos = (int32_t)sb.slot, grp = (int32_t)sb.group + (int32_t)blockIdx.y * gx;
+  const int32_t pos = (int32_t)sb.slot, run = (int32_t)sb.group + (int32_t)blockIdx.y * gx;
+  const int32_t grp = RANGED ? run / rsplit : run;
   if (pos >= n || grp >= groups) return;  // padding of the grid
   const ScatterSlot sl = slots[pos];
   const int32_t sid = sl.pad;
@@ -342,13 +344,14 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
       }
     }
     fetch(batch + 1);
-    const int nranges = RANGED ? 1 << (log2m - log2acc) : 1;
-    for (int range = 0; range < nranges; ++range) {
+    const int nranges = RANGED ? 1 << (log2m - log2acc) : 1, rstep = RANGED ? rsplit : 1;
+    const int range0 = RANGED ? run - grp * rsplit : 0;
+    for (int range = range0; range < nranges; range += rstep) {
       const uint32_t rlo = (uint32_t)range << (3 + log2acc), rlen = 8u << log2acc;
       for (int rb = 0; rb < rows; rb += kRowChunk) {
         const int re = min(rows, rb + kRowChunk);
         if (rb > 0) __syncthreads();  // the last chunk's readers are done
-        if (range == 0 || rows > kRowChunk) {
+        if (range == range0 || rows > kRowChunk) {
           // rows, then (few) columns
           for (int r = rb + tid; r < re + (few ? L : 0); r += NT) {
             uint32_t w[SB];
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
           }
         }
         __syncthreads();
-        if (few && range == 0) {
+        if (few && range == range0) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             uint32_t w[SB];
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
         }
       }
       __syncthreads();
-      if (range == nranges - 1) put(batch + 1);
+      if (range + rstep >= nranges) put(batch + 1);
       // Sketches out, accumulators cleared: (positive bank minus negative bank)
       // 2^-scale, four buckets per thread and 16-byte accesses when a sketch
       // has at least four.
@@ -1500,6 +1503,11 @@ constexpr size_t kWideLds = 81920;
 // per block, 2.96 with 32).
 constexpr int64_t kSlotBlocks = 2048, kBlockSamples = 16;
 constexpr int64_t kNarrowSlot = 16384;  // entries
+// One to a CU.  A FP64 lattice of 16 tensors, bond 16, m = 65536, 4 samples: 109
+// us per call with a slot's ranges in one block, 85 so; up to 512 blocks (a
+// second round, half as long) cost a lattice of 9 of bond 9, 8 samples, 96
+// against 90.
+constexpr int64_t kRangeBlocks = 256;
 template <typename T, typename A, int SB, int BANKS, int NT, bool RANGED = false>
 int scatter_launch(const M1Launch &L, hipStream_t st) {
   const int64_t n = L.n_big;
@@ -1511,14 +1519,19 @@ int scatter_launch(const M1Launch &L, hipStream_t st) {
   const int64_t batches = (L.samples + SB - 1) / SB;
   const int64_t gs = std::max<int64_t>(1, std::min({batches, kBlockSamples / SB, n * batches / kSlotBlocks}));
   const int64_t groups = (batches + gs - 1) / gs;
+  // The ranges of a group on blocks of their own while there is a CU for each
+  // (a block fills one).
+  int64_t rsplit = 1;
+  if (RANGED)
+    while (rsplit < (int64_t)1 << (L.log2m - kMaxLog2Acc) && 2 * rsplit * n * groups <= kRangeBlocks) rsplit *= 2;
   // groups per grid row: the grid's x extent stays within 2^31 threads
-  const int64_t slots8 = (n + 7) / 8 * 8;
-  const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(groups, ((int64_t)1 << 21) / slots8));
-  const dim3 grid(slot_blocks((uint32_t)n, (uint32_t)gx), (unsigned)((groups + gx - 1) / gx));
+  const int64_t slots8 = (n + 7) / 8 * 8, runs = groups * rsplit;
+  const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(runs, ((int64_t)1 << 21) / slots8));
+  const dim3 grid(slot_blocks((uint32_t)n, (uint32_t)gx), (unsigned)((runs + gx - 1) / gx));
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, L.slots, (int32_t)n, L.modes, L.data, L.tables, L.W,
                      L.samples, L.log2m, L.n_slots, reinterpret_cast<A *>(L.ybuf),
                      L.record_bound ? nullptr : L.slot_bound, L.slot_bound, (int32_t)gs, (int32_t)groups,
-                     (int32_t)gx);
+                     (int32_t)gx, (int32_t)rsplit);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }
