@@ -1043,8 +1043,13 @@ __global__ __launch_bounds__(256) void m1_big_cols_kernel(const int32_t *__restr
     for (int q = tid; q < CB * (kBigN2 / 4); q += 256) {
       A2 *zt = z + (q >> 6) * kBigStr;
       const int qq = q & 63, k = qq & (h - 1), base = ((qq >> (lg - 1)) << (lg + 1)) + k;
-      big_radix4(zt[pad32(base)], zt[pad32(base + h)], zt[pad32(base + 2 * h)], zt[pad32(base + 3 * h)],
-                 tw2[pad32(k << (8 - lg))], tw2[pad32(k << (7 - lg))], tw2[pad32((k + h) << (7 - lg))]);
+      // (copies: through references into LDS each stage would store and load its points)
+      A2 z0 = zt[pad32(base)], z1 = zt[pad32(base + h)], z2 = zt[pad32(base + 2 * h)], z3 = zt[pad32(base + 3 * h)];
+      big_radix4(z0, z1, z2, z3, tw2[pad32(k << (8 - lg))], tw2[pad32(k << (7 - lg))], tw2[pad32((k + h) << (7 - lg))]);
+      zt[pad32(base)] = z0;
+      zt[pad32(base + h)] = z1;
+      zt[pad32(base + 2 * h)] = z2;
+      zt[pad32(base + 3 * h)] = z3;
     }
     __syncthreads();
   }
