@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void stream_update_kernel(
   }
 }
 
-// At least m updates: a block adds its share of them to one sample's sketch in
+// Many updates: a block adds its share of them to one sample's sketch in
 // LDS, in FP64, and the sums to the sketch in one coalesced pass.  Adds to
 // random words of memory run at 22 per ns whatever their type and wherever
 // their blocks are, adds of whole lines at 226, FP64 adds in LDS at 1670
@@ -138,6 +138,11 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4 *__restrict__ p, i
 // LDS of 128 KB at most; blocks that keep every CU at work.
 constexpr int kMaxLog2Share = 14;
 constexpr int64_t kShareBlocks = 1024;
+// A share's pass over its m words takes as long as 16 m adds to random words of
+// memory (direct / shares, FP32: m = 16384, 16384 updates, one sample 4.6 / 15.9
+// us, 16 samples 16.2 / 16.2, 64 samples 53 / 17; m = 4096, 16384 updates, one
+// sample 4.6 / 5.7, four 5.9 / 5.8, 16 16.0 / 5.9).
+constexpr int64_t kShareAdds = 16;
 
 }  // namespace
 
@@ -157,7 +162,7 @@ int launch_stream_update(const ModeDesc *modes, int mode0, int q, int64_t size, 
   };
   double *y64 = reinterpret_cast<double *>(ybuf);
   float *y32 = reinterpret_cast<float *>(ybuf);
-  if (n >= m && log2m <= kMaxLog2Share) {
+  if (n >= m && n * S >= kShareAdds * m && log2m <= kMaxLog2Share) {
     // shares of at least m updates, so that the pass over the sketch does not
     // outweigh them, and blocks for the chip
     const int64_t shares = std::max<int64_t>(1, std::min(n / m, (kShareBlocks + S - 1) / S));
