@@ -9,7 +9,6 @@
 // tensor's slots), with the complement bucket on the second mode of each
 // contraction (Def. 14), exactly as the scatter would for that entry.
 #include <algorithm>
-#include <type_traits>
 
 #include "tn_internal.h"
 
@@ -20,22 +19,20 @@ constexpr int kUpdates = 4;  // per thread and round, their index loads in fligh
 
 // The words of kUpdates updates u0, u0 + step, ... below n: bucket, sign of the
 // update in bit 31, and the update x; in[k] false outside the range or the
-// tensor.  WIDE: tensors of 2^32 entries or more; else a digit takes one
-// multiplication and a correction, by inv = floor((2^32 - 1) / n): for
-// i < 2^32, i inv / 2^32 is less than one below i / n.
-template <bool WIDE>
+// tensor.  A digit takes one multiplication and a correction, by inv =
+// floor((2^32 - 1) / n): for i < 2^32 (tensors have at most 2^31 entries), i
+// inv / 2^32 is less than one below i / n.
 __device__ __forceinline__ void update_words(const ModeDesc *__restrict__ modes, int mode0, int q, int64_t size,
                                              const int32_t *__restrict__ tab, uint32_t m, int64_t u0, int64_t step,
                                              int64_t n, const int64_t *__restrict__ idx,
                                              const double *__restrict__ delta, bool *in, uint32_t *b, double *x) {
-  using I = typename std::conditional<WIDE, uint64_t, uint32_t>::type;
   const uint32_t mask = m - 1;
-  I i[kUpdates];
+  uint32_t i[kUpdates];
 #pragma unroll
   for (int k = 0; k < kUpdates; ++k) {
     const int64_t u = min(u0 + k * step, n - 1), e = idx[u];
     in[k] = u0 + k * step < n && e >= 0 && e < size;  // outside the tensor: ignored
-    i[k] = in[k] ? (I)e : 0;
+    i[k] = in[k] ? (uint32_t)e : 0u;
     x[k] = delta[u];
     b[k] = 0;
   }
@@ -44,19 +41,12 @@ __device__ __forceinline__ void update_words(const ModeDesc *__restrict__ modes,
     const uint32_t dn = (uint32_t)md.n, inv = 0xffffffffu / dn;
 #pragma unroll
     for (int k = 0; k < kUpdates; ++k) {
-      uint32_t d;
-      if constexpr (WIDE) {
-        d = (uint32_t)(i[k] % dn);
-        i[k] /= dn;
-      } else {
-        uint32_t quo = __umulhi(i[k], inv);
-        d = i[k] - quo * dn;
-        if (d >= dn) {
-          d -= dn;
-          ++quo;
-        }
-        i[k] = quo;
+      uint32_t quo = __umulhi(i[k], inv), d = i[k] - quo * dn;
+      if (d >= dn) {
+        d -= dn;
+        ++quo;
       }
+      i[k] = quo;
       const uint32_t v = (uint32_t)tab[md.table_off + d];
       uint32_t h = v & ~kSignBit;
       if (md.comp) h = (m - h) & mask;
@@ -70,7 +60,7 @@ __device__ __forceinline__ void update_words(const ModeDesc *__restrict__ modes,
 
 // Few updates: straight into the sketch.  A block's 256 threads are 2^lg
 // updates x (256 >> lg) samples, lg as large as the call's updates fill.
-template <typename A, bool WIDE>
+template <typename A>
 __global__ __launch_bounds__(256) void stream_update_kernel(
     const ModeDesc *__restrict__ modes, int mode0, int q, int64_t size, const int32_t *__restrict__ tables,
     int64_t W, int64_t S, int log2m, int64_t sample_stride, int64_t slot_off, A *__restrict__ ybuf, int64_t n,
@@ -82,7 +72,7 @@ __global__ __launch_bounds__(256) void stream_update_kernel(
     bool in[kUpdates];
     uint32_t b[kUpdates];
     double x[kUpdates];
-    update_words<WIDE>(modes, mode0, q, size, tables + s * W, m, u0, lanes, n, idx, delta, in, b, x);
+    update_words(modes, mode0, q, size, tables + s * W, m, u0, lanes, n, idx, delta, in, b, x);
     A *y = ybuf + s * sample_stride + slot_off;
 #pragma unroll
     for (int k = 0; k < kUpdates; ++k)
@@ -96,7 +86,7 @@ __global__ __launch_bounds__(256) void stream_update_kernel(
 // their blocks are, adds of whole lines at 226, FP64 adds in LDS at 1670
 // (FP32 ones, a compare-and-swap loop there, at 200).
 constexpr int kShareThreads = 512;
-template <typename A, bool WIDE>
+template <typename A>
 __global__ __launch_bounds__(kShareThreads) void stream_share_kernel(
     const ModeDesc *__restrict__ modes, int mode0, int q, int64_t size, const int32_t *__restrict__ tables,
     int64_t W, int64_t S, int log2m, int64_t sample_stride, int64_t slot_off, A *__restrict__ ybuf, int64_t n,
@@ -112,8 +102,7 @@ __global__ __launch_bounds__(kShareThreads) void stream_share_kernel(
       bool in[kUpdates];
       uint32_t b[kUpdates];
       double x[kUpdates];
-      update_words<WIDE>(modes, mode0, q, size, tables + s * W, m, u0 + tid, kShareThreads, last, idx, delta, in, b,
-                         x);
+      update_words(modes, mode0, q, size, tables + s * W, m, u0 + tid, kShareThreads, last, idx, delta, in, b, x);
 #pragma unroll
       for (int k = 0; k < kUpdates; ++k)
         if (in[k])
@@ -151,7 +140,6 @@ int launch_stream_update(const ModeDesc *modes, int mode0, int q, int64_t size, 
                          const int64_t *idx, const double *delta, hipStream_t st) {
   if (n == 0) return TN_OK;
   const int64_t m = 1ll << log2m;
-  const bool wide = size > 0xffffffffll;
   auto run = [&](auto kern, dim3 grid, int threads, size_t lds, auto *y, auto split) -> int {
     if (lds > 65536)
       TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -160,8 +148,6 @@ int launch_stream_update(const ModeDesc *modes, int mode0, int q, int64_t size, 
     TN_HIP_CHECK(hipGetLastError());
     return TN_OK;
   };
-  double *y64 = reinterpret_cast<double *>(ybuf);
-  float *y32 = reinterpret_cast<float *>(ybuf);
   if (n >= m && n * S >= kShareAdds * m && log2m <= kMaxLog2Share) {
     // shares of at least m updates, so that the pass over the sketch does not
     // outweigh them, and blocks for the chip
@@ -170,20 +156,16 @@ int launch_stream_update(const ModeDesc *modes, int mode0, int q, int64_t size, 
     const dim3 grid((unsigned)shares, (unsigned)std::min<int64_t>(S, 65535));
     const size_t lds = (size_t)m * 8;
     if (dtype == TN_F64)
-      return wide ? run(stream_share_kernel<double, true>, grid, kShareThreads, lds, y64, share)
-                  : run(stream_share_kernel<double, false>, grid, kShareThreads, lds, y64, share);
-    return wide ? run(stream_share_kernel<float, true>, grid, kShareThreads, lds, y32, share)
-                : run(stream_share_kernel<float, false>, grid, kShareThreads, lds, y32, share);
+      return run(stream_share_kernel<double>, grid, kShareThreads, lds, reinterpret_cast<double *>(ybuf), share);
+    return run(stream_share_kernel<float>, grid, kShareThreads, lds, reinterpret_cast<float *>(ybuf), share);
   }
   int lg = 0;  // lanes along the updates: the call's updates, kUpdates to a lane
   while (lg < 8 && ((int64_t)kUpdates << lg) < n) ++lg;
   const int64_t per = (int64_t)kUpdates << lg, rows = 256 >> lg;
   const dim3 grid((unsigned)((n + per - 1) / per), (unsigned)std::min<int64_t>((S + rows - 1) / rows, 65535));
   if (dtype == TN_F64)
-    return wide ? run(stream_update_kernel<double, true>, grid, 256, 0, y64, lg)
-                : run(stream_update_kernel<double, false>, grid, 256, 0, y64, lg);
-  return wide ? run(stream_update_kernel<float, true>, grid, 256, 0, y32, lg)
-              : run(stream_update_kernel<float, false>, grid, 256, 0, y32, lg);
+    return run(stream_update_kernel<double>, grid, 256, 0, reinterpret_cast<double *>(ybuf), lg);
+  return run(stream_update_kernel<float>, grid, 256, 0, reinterpret_cast<float *>(ybuf), lg);
 }
 
 // Zero a 16-byte-aligned buffer with a kernel (graph-safe, unlike a memset
