@@ -107,12 +107,14 @@ struct PermDesc {
   int64_t in_stride[kMaxLabels];
 };
 constexpr int kPermPer = 4;
+constexpr int64_t kPermGridX = (int64_t)1 << 22;  // blocks in x: 2^32 threads are refused (2^34 entries)
+static_assert(kPermGridX * 256 <= 0xffffffffll, "threads in x");
 
 template <bool WIDE>
 __global__ __launch_bounds__(256) void permute_f64_kernel(PermDesc d, const double *__restrict__ in, int64_t n,
                                                           double *__restrict__ out) {
   using I = typename std::conditional<WIDE, int64_t, uint32_t>::type;
-  const int64_t o0 = (int64_t)blockIdx.x * (256 * kPermPer) + threadIdx.x;
+  const int64_t o0 = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (256 * kPermPer) + threadIdx.x;
   I rem[kPermPer];
   int64_t off[kPermPer];
 #pragma unroll
@@ -417,8 +419,9 @@ int permute(Mem &mem, DTensor *T, const std::vector<int> &to) {
   }
   if (!mem.dry) {
     auto kern = out.size > 0xffffffffll ? permute_f64_kernel<true> : permute_f64_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((out.size + 256 * kPermPer - 1) / (256 * kPermPer))), dim3(256), 0,
-                       mem.st, d, T->ptr, out.size, out.ptr);
+    const int64_t blocks = (out.size + 256 * kPermPer - 1) / (256 * kPermPer), gx = std::min(blocks, kPermGridX);
+    hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)((blocks + gx - 1) / gx)), dim3(256), 0, mem.st, d, T->ptr,
+                       out.size, out.ptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
       mem.release(&out);
