@@ -6,6 +6,8 @@
 //                        activations live in LDS; it writes predictions and/or
 //                        the block's partial gradient (sums over its rows) and
 //                        partial loss, FP64.
+//   mlp_rows_kernel    : predictions of narrow networks for many rows, a lane
+//                        to a row.
 //   mlp_reduce_kernel  : sums the blocks' partials in a fixed order
 //                        (deterministic), 64 parameters per block, and either
 //                        exports the gradient or applies a bias-corrected Adam
@@ -219,6 +221,91 @@ __global__ __launch_bounds__(512) void mlp_fwd_bwd_kernel(
   }
 }
 
+// Predictions of narrow networks (H <= kRowUnits) for many rows: a block's lanes
+// are 64 rows, its waves (mlp_row_waves) take four units each in turn.  The rows'
+// inputs, kRowInputs at a time, and both layers live in LDS unit by unit,
+// kRowStride floats each; weights come through the scalar cache, four units' at
+// a time.  Every dot product runs in the order of its index, as in
+// mlp_fwd_bwd_kernel, whose lanes are units and are left idle by a narrow layer.
+// Bound by vector instructions, most of them tanh's, and by the inputs' loads.
+constexpr int kRowUnits = 32, kRowStride = 65, kRowInputs = 32;
+// Waves with units of their own, or four where the inputs take several loads
+// (262144 rows of 256 inputs and 4 units: 101 us with one wave, 69 with four;
+// 1048576 rows of 8 inputs and one unit: 19, 32).
+int mlp_row_waves(int D, int H) { return D > kRowInputs ? 4 : std::min(4, (H + 3) / 4); }
+__global__ __launch_bounds__(256) void mlp_rows_kernel(const float *__restrict__ params, int D, int H,
+                                                      const float *__restrict__ X, int64_t n,
+                                                      float *__restrict__ pred) {
+  extern __shared__ __align__(16) float sm[];
+  float *h1 = sm, *h2 = h1 + H * kRowStride;  // [H][kRowStride]
+  float *xs = h2 + H * kRowStride;            // [min(D, kRowInputs)][kRowStride]
+  const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), step = nth / 16;  // four units per wave
+  const int64_t base = (int64_t)blockIdx.x * 64;
+  const int rows = (int)min((int64_t)64, n - base);
+  const float *Xb = X + base * D;
+  // Units' sums over ni inputs, four units at a time: from(unit) to put(unit, sum).
+  auto layer = [&](const float *__restrict__ w, int ws, int ni, const float *in, auto from, auto put) {
+    for (int j = 4 * wave; j < H; j += step) {
+      float a[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = from(min(j + q, H - 1));
+      const float *w0 = w + j * ws;
+      const int s1 = j + 1 < H ? ws : 0, s2 = j + 2 < H ? 2 * ws : 0, s3 = j + 3 < H ? 3 * ws : 0;
+#pragma unroll 4
+      for (int i = 0; i < ni; ++i) {
+        const float x = in[i * kRowStride + lane];
+        a[0] = fmaf(w0[i], x, a[0]);
+        a[1] = fmaf(w0[i + s1], x, a[1]);
+        a[2] = fmaf(w0[i + s2], x, a[2]);
+        a[3] = fmaf(w0[i + s3], x, a[3]);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (j + q < H) put(j + q, a[q]);
+    }
+  };
+  const float *pb1 = params + H * D, *pW2 = pb1 + H, *pb2 = pW2 + H * H, *pW3 = pb2 + H;
+  for (int d0 = 0; d0 < D; d0 += kRowInputs) {
+    const int nd = min(kRowInputs, D - d0);
+    __syncthreads();  // the last inputs' readers are done
+    if (nd == kRowInputs) {
+      constexpr int G = 8;  // loads in flight
+      for (int i0 = tid; i0 < 64 * kRowInputs; i0 += nth * G) {
+        float v[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const int i = i0 + nth * g;
+          v[g] = Xb[(int64_t)min(i / kRowInputs, rows - 1) * D + d0 + i % kRowInputs];
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const int i = i0 + nth * g;
+          xs[i % kRowInputs * kRowStride + i / kRowInputs] = v[g];
+        }
+      }
+    } else {
+      for (int i = tid; i < rows * nd; i += nth) {
+        const int s = i / nd, d = i - s * nd;
+        xs[d * kRowStride + s] = Xb[s * D + d0 + d];
+      }
+    }
+    __syncthreads();
+    const bool last = d0 + nd == D;
+    layer(params + d0, D, nd, xs, [&](int j) { return d0 == 0 ? pb1[j] : h1[j * kRowStride + lane]; },
+          [&](int j, float a) { h1[j * kRowStride + lane] = last ? tanhf(a) : a; });
+  }
+  __syncthreads();
+  layer(pW2, H, H, h1, [&](int j) { return pb2[j]; }, [&](int j, float a) { h2[j * kRowStride + lane] = tanhf(a); });
+  __syncthreads();
+  if (tid >= rows) return;
+  float o = pW3[H];
+#pragma unroll 8
+  for (int j = 0; j < H; ++j) o = fmaf(pW3[j], h2[j * kRowStride + tid], o);
+  pred[base + tid] = o;
+}
+static_assert(4 * kRowStride * (2 * kRowUnits + kRowInputs) <= 65536, "LDS without an attribute");
+
 // mode 0: grad[p] = sum; mode 1: Adam.  scalar[0] = summed loss * loss_scale and
 // scalar[1] += summed loss * epoch_scale (the epoch's mean loss, batch by batch).
 // A block takes 64 parameters; its eight waves each sum a run of the partials,
@@ -283,6 +370,13 @@ int ensure_partial(tn_mlp *net, int64_t blocks) {
   return TN_OK;
 }
 
+size_t mlp_rows_lds(int D, int H) { return 4 * (size_t)kRowStride * (size_t)(std::min(D, kRowInputs) + 2 * H); }
+// Whether predictions take a lane per row: with two tiles of 16 rows or more to
+// a CU.  By tiles / by rows: 1048576 rows of 8 inputs and 16 units 659 / 56 us,
+// of 8 and 32 816 / 108; 16384 rows of 100 and 4 23.6 / 9.6; 8192 rows of 256
+// and 16 22.0 / 18.3, 4096 of them 11.7 / 18.3.
+bool mlp_by_rows(int H, int64_t rows) { return H <= kRowUnits && rows >= 8192; }
+
 // Tiles of 16 rows per block, and blocks, for a batch of `rows` rows.
 int mlp_tiles(int64_t rows) { return rows > kManyTiles * kTile ? 4 : 1; }
 int64_t mlp_blocks(int64_t rows) {
@@ -298,6 +392,14 @@ int fwd_bwd(tn_mlp *net, const float *X, const float *y, int64_t row0, int64_t r
   if (grad) {
     int rc = ensure_partial(net, blocks);
     if (rc != TN_OK) return rc;
+  }
+  if (!grad && mlp_by_rows(net->H, rows)) {
+    hipLaunchKernelGGL(mlp_rows_kernel, dim3((unsigned)((rows + 63) / 64)),
+                       dim3(64 * mlp_row_waves(net->D, net->H)),
+                       mlp_rows_lds(net->D, net->H), st, net->d_params, net->D, net->H, X + row0 * net->D, rows,
+                       pred + row0);
+    TN_HIP_CHECK(hipGetLastError());
+    return TN_OK;
   }
   hipLaunchKernelGGL(mlp_fwd_bwd_kernel, dim3((unsigned)blocks), dim3(512), net->lds, st,
                      net->d_params, net->D, net->H, X, y, row0, row0 + rows < n ? row0 + rows : n,
