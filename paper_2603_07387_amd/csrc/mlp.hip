@@ -68,6 +68,8 @@ __global__ __launch_bounds__(512) void mlp_fwd_bwd_kernel(
     const float *__restrict__ y, int64_t row0, int64_t n, float scale, float *__restrict__ pred,
     double *__restrict__ partial, int64_t P, int tiles) {
   extern __shared__ __align__(16) float sm[];
+  const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (row0 + block * tiles * kTile >= n) return;  // padding of the grid
   const int D1 = D + 1, H1 = H + 1, H4 = mlp_up4(H);
   float *W1 = sm;                 // [H][D + 1]
   float *W2 = W1 + H * D1;        // [H][H + 1]
@@ -95,9 +97,9 @@ __global__ __launch_bounds__(512) void mlp_fwd_bwd_kernel(
     W3[j] = pb2[H + j];
   }
   if (tid == 0) b3[0] = pb2[2 * H];
-  double *out = partial ? partial + (int64_t)blockIdx.x * (P + 1) : nullptr;
+  double *out = partial ? partial + block * (P + 1) : nullptr;
   for (int tile = 0; tile < tiles; ++tile) {
-    const int64_t base = row0 + ((int64_t)blockIdx.x * tiles + tile) * kTile;
+    const int64_t base = row0 + (block * tiles + tile) * kTile;
     if (tile > 0) {
       if (base >= n) break;  // uniform over the block
       __syncthreads();       // the last tile's readers are done
@@ -241,7 +243,8 @@ __global__ __launch_bounds__(256) void mlp_rows_kernel(const float *__restrict__
   float *xs = h2 + H * kRowStride;            // [min(D, kRowInputs)][kRowStride]
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), step = nth / 16;  // four units per wave
-  const int64_t base = (int64_t)blockIdx.x * 64;
+  const int64_t base = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 64;
+  if (base >= n) return;  // padding of the grid
   const int rows = (int)min((int64_t)64, n - base);
   const float *Xb = X + base * D;
   // Units' sums over ni inputs, four units at a time: from(unit) to put(unit, sum).
@@ -370,6 +373,13 @@ int ensure_partial(tn_mlp *net, int64_t blocks) {
   return TN_OK;
 }
 
+// Blocks in x and y: the runtime refuses 2^32 threads in x (2^29 rows).
+constexpr int64_t kGridX = (int64_t)1 << 21;
+static_assert(kGridX * 512 <= 0xffffffffll, "threads in x");
+dim3 mlp_grid(int64_t blocks) {
+  const int64_t gx = std::min(blocks, kGridX);
+  return dim3((unsigned)gx, (unsigned)((blocks + gx - 1) / gx));
+}
 size_t mlp_rows_lds(int D, int H) { return 4 * (size_t)kRowStride * (size_t)(std::min(D, kRowInputs) + 2 * H); }
 // Whether predictions take a lane per row: with two tiles of 16 rows or more to
 // a CU.  By tiles / by rows: 1048576 rows of 8 inputs and 16 units 659 / 56 us,
@@ -394,14 +404,13 @@ int fwd_bwd(tn_mlp *net, const float *X, const float *y, int64_t row0, int64_t r
     if (rc != TN_OK) return rc;
   }
   if (!grad && mlp_by_rows(net->H, rows)) {
-    hipLaunchKernelGGL(mlp_rows_kernel, dim3((unsigned)((rows + 63) / 64)),
-                       dim3(64 * mlp_row_waves(net->D, net->H)),
+    hipLaunchKernelGGL(mlp_rows_kernel, mlp_grid((rows + 63) / 64), dim3(64 * mlp_row_waves(net->D, net->H)),
                        mlp_rows_lds(net->D, net->H), st, net->d_params, net->D, net->H, X + row0 * net->D, rows,
                        pred + row0);
     TN_HIP_CHECK(hipGetLastError());
     return TN_OK;
   }
-  hipLaunchKernelGGL(mlp_fwd_bwd_kernel, dim3((unsigned)blocks), dim3(512), net->lds, st,
+  hipLaunchKernelGGL(mlp_fwd_bwd_kernel, mlp_grid(blocks), dim3(512), net->lds, st,
                      net->d_params, net->D, net->H, X, y, row0, row0 + rows < n ? row0 + rows : n,
                      (float)(1.0 / (double)rows), pred, grad ? net->d_partial : nullptr, net->P, mlp_tiles(rows));
   TN_HIP_CHECK(hipGetLastError());
