@@ -1,5 +1,7 @@
 // Count-sketch hash tables on the device (the hash family of tn_sketch.h), one
 // packed int32 entry per (sample, stream, index).
+#include <algorithm>
+
 #include "hash_device.h"
 #include "tn_internal.h"
 
@@ -14,8 +16,9 @@ template <bool WAVE>
 __global__ __launch_bounds__(256) void hashgen_kernel(const StreamDesc *__restrict__ streams, int64_t n_streams,
                                                       int64_t W, int64_t sample0, int64_t samples, int lg,
                                                       uint32_t mask, int32_t *__restrict__ out) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x, pairs = n_streams * samples;
-  const int64_t pair = WAVE ? (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : gid >> lg;
+  const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, gid = block * 256 + threadIdx.x;
+  const int64_t pairs = n_streams * samples;
+  const int64_t pair = WAVE ? block * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : gid >> lg;
   if (pair >= pairs) return;
   const int64_t r = pairs <= 0xffffffffll ? (int64_t)((uint32_t)pair / (uint32_t)n_streams) : pair / n_streams;
   const StreamDesc sd = streams[pair - r * n_streams];
@@ -56,12 +59,13 @@ int launch_hashgen(const StreamDesc *streams, int64_t n_streams, int64_t W, int6
          (pairs << lg < (lg < 2 ? (int64_t)1 << 20 : (int64_t)1 << 16) ||
           max_n >> lg > kLaneIndices || max_n > kLongStream))
     ++lg;
-  const int64_t blocks = ((pairs << lg) + 255) / 256;
-  if (blocks > 0x7fffffff)
+  // (the runtime refuses 2^32 threads in x)
+  const int64_t blocks = ((pairs << lg) + 255) / 256, gx = std::min<int64_t>(blocks, 1 << 22), gy = (blocks + gx - 1) / gx;
+  if (gy > 65535)
     return set_error(TN_ERR_UNSUPPORTED, "hashgen: %lld samples x %lld streams per launch", (long long)samples,
                      (long long)n_streams);
-  hipLaunchKernelGGL(lg == 6 ? hashgen_kernel<true> : hashgen_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, streams, n_streams, W, sample0, samples,
-                     lg, (uint32_t)(m - 1), out);
+  hipLaunchKernelGGL(lg == 6 ? hashgen_kernel<true> : hashgen_kernel<false>, dim3((unsigned)gx, (unsigned)gy), dim3(256),
+                     0, st, streams, n_streams, W, sample0, samples, lg, (uint32_t)(m - 1), out);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }

@@ -28,3 +28,24 @@ def test_long_streams(orc, S, dims):
             v = got[s, off:off + n]
             assert np.array_equal(v & 0x7FFFFFFF, h), (s, sid)
             assert np.array_equal(np.where(v < 0, -1, 1), sg), (s, sid)
+
+
+def test_more_threads_than_a_grid_row(orc):
+    """One stream of 600 indices among 3003, 24000 samples: 64 lanes to each of 72 million pairs is more than 2^32
+    threads."""
+    import torch
+    import paper_2603_07387_amd as T
+    x, one = torch.ones(600, 1, device="cuda"), torch.ones(1, 1, device="cuda")
+    edges = [(1, 2), (3, 4), (5, 0)]
+    specs = [T.NetworkSpec([2, 2, 2], [600, 1, 1, 1, 1, 600], edges, tensors=[x, one, x.view(1, 600)])]
+    specs += [T.NetworkSpec([2, 2, 2], [1] * 6, edges, tensors=[one] * 3)] * 1000
+    plan = T.Plan(specs, T.TN_CYCLIC, 64, 24000, 9)
+    got = plan.hashes()
+    streams = plan.streams()
+    for k in (0, 1, 2, 1500, 3002):
+        net, sid, n, off = streams[k]
+        for s in (0, 11999, 23999):
+            h, sg = orc.hash_table(9 + net, s, sid, n, 64)
+            v = got[s, off:off + n].cpu().numpy()
+            assert np.array_equal(v & 0x7FFFFFFF, h), (k, s)
+            assert np.array_equal(np.where(v < 0, -1, 1), sg), (k, s)
