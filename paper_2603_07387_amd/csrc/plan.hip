@@ -18,7 +18,12 @@ namespace tn {
 namespace {
 
 constexpr int kMaxRowsPerSlot = 2048;
-constexpr size_t kWorkspaceBudget = (size_t)4 << 30;  // tables + sketches per pass (16 samples of the batch of 4096 networks: 2 GiB)
+// Tables + sketches per pass.  Two GiB while three quarters of the device's
+// memory are free (the batch of 4096 networks in one pass of 16 samples: 2.64 ms
+// per call, 2.91 in two of 8; four GiB 2.65; 48 lattices at m = 65536, 6 samples,
+// 1.27, 1.48, 1.28), one otherwise and where that much cannot be had: a program
+// of many plans keeps room for them.
+constexpr size_t kWorkspaceBudget = (size_t)1 << 30, kWorkspaceLarge = (size_t)2 << 30;
 constexpr int64_t kScatterFill = 256;  // scatter blocks to keep (one per CU) when taking more samples per pass
 constexpr int64_t kCombineSplitBlocks = 1024;            // combine blocks to aim for when splitting
 constexpr size_t kCombineSplitBudget = (size_t)256 << 20;  // bytes of partial spectra
@@ -227,24 +232,44 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   if (lds_for(p->sb) > p->max_lds)
     return set_error(TN_ERR_UNSUPPORTED, "cyclic method: scatter needs %zu bytes of LDS", lds_for(p->sb));
 
-  const size_t per_sample = (size_t)p->W * 4 + p->h_slots.size() * (size_t)p->m * as +
+  // m >= 2^15, FP32 sketches, every tensor one slot, and its words in the LDS
+  // beside the transforms: the scatter takes the combine's first pass too
+  // (resident plans keep the sketches themselves).
+  if (p->two_pass && p->dtype != TN_F64 && !(p->flags & TN_FLAG_RESIDENT) &&
+      p->h_slots.size() + 1 == p->h_tslot.size()) {
+    for (const ScatterSlot &sl : p->h_slots) {
+      p->max_cols = std::max(p->max_cols, sl.L);
+      p->max_rows = std::max(p->max_rows, sl.rows);
+    }
+    p->big_scatter = m1_big_scatter_lds(p->max_cols, p->max_rows) <= p->max_lds;
+  }
+  const size_t sketch_bytes = p->h_slots.size() * (size_t)p->m * as;
+  const size_t per_sample = (size_t)p->W * 4 + sketch_bytes +
                             (p->two_pass ? (size_t)(p->n_tensors + p->n_nets) / 2 * (size_t)p->m * 2 * as +
                                                (size_t)p->n_nets * kBigPartials * 8
                                          : 0);
-  int64_t chunk = (int64_t)std::max<size_t>(1, kWorkspaceBudget / std::max<size_t>(1, per_sample));
-  chunk = std::min<int64_t>(chunk, p->S);
-  chunk = std::min<int64_t>(chunk, 65535);
-  if (p->flags & TN_FLAG_RESIDENT) {
-    // every sample's sketches and hash tables stay in device memory
-    if (p->S > 65535 || (double)per_sample * (double)p->S > (double)kResidentBudget)
-      return set_error(TN_ERR_UNSUPPORTED, "resident sketches: %lld samples of %zu bytes exceed the %zu-byte limit",
-                       (long long)p->S, per_sample, kResidentBudget);
-    chunk = p->S;
+  // every sample's sketches and hash tables of a resident plan stay in device memory
+  if ((p->flags & TN_FLAG_RESIDENT) &&
+      (p->S > 65535 || (double)per_sample * (double)p->S > (double)kResidentBudget))
+    return set_error(TN_ERR_UNSUPPORTED, "resident sketches: %lld samples of %zu bytes exceed the %zu-byte limit",
+                     (long long)p->S, per_sample, kResidentBudget);
+  auto set_chunk = [&](size_t budget) {
+    int64_t chunk = (int64_t)std::max<size_t>(1, budget / std::max<size_t>(1, per_sample));
+    chunk = std::min<int64_t>({chunk, p->S, 65535});
+    if (p->flags & TN_FLAG_RESIDENT) chunk = p->S;
+    p->chunk_alloc = chunk;
+    if (chunk > 16 && !(p->flags & TN_FLAG_RESIDENT)) chunk = chunk / 16 * 16;  // a multiple of every samples-per-pass choice
+    p->chunk = chunk;
+  };
+  size_t budget = kWorkspaceBudget;
+  if (const char *env = getenv("TN_WORKSPACE_MB")) {  // (tests)
+    budget = (size_t)std::max(1ll, atoll(env)) << 20;
+  } else {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) (void)hipGetLastError();
+    else if (free_b / 3 >= total_b / 4) budget = kWorkspaceLarge;
   }
-  p->chunk_alloc = chunk;
-  if (chunk > 16 && !(p->flags & TN_FLAG_RESIDENT)) chunk = chunk / 16 * 16;  // a multiple of every samples-per-pass choice
-  p->chunk = chunk;
-  int64_t table_samples = chunk;
+  set_chunk(budget);
 
   // Persistent fused kernel: per-tensor headroom, per-network work (items are
   // handed out largest first), then a default configuration (one bank, as
@@ -270,7 +295,6 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     }
     int64_t fc = (int64_t)std::max<size_t>(1, kWorkspaceBudget / std::max<size_t>(1, (size_t)p->W * 4));
     p->fused_chunk_cap = std::min<int64_t>({fc, p->S, 65535});
-    table_samples = std::max(table_samples, p->fused_chunk_cap);
     int rc0;
     if ((rc0 = upload(&p->d_tensor_lgn, lgn)) != TN_OK) return rc0;
     if ((rc0 = dev_alloc(&p->d_counter, 1)) != TN_OK) return rc0;
@@ -286,17 +310,6 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   int rc;
   if ((rc = upload(&p->d_streams, p->h_streams)) != TN_OK) return rc;
   if ((rc = upload(&p->d_modes, p->h_modes)) != TN_OK) return rc;
-  // m >= 2^15, FP32 sketches, every tensor one slot, and its words in the LDS
-  // beside the transforms: the scatter takes the combine's first pass too
-  // (resident plans keep the sketches themselves).
-  if (p->two_pass && p->dtype != TN_F64 && !(p->flags & TN_FLAG_RESIDENT) &&
-      p->h_slots.size() + 1 == p->h_tslot.size()) {
-    for (const ScatterSlot &sl : p->h_slots) {
-      p->max_cols = std::max(p->max_cols, sl.L);
-      p->max_rows = std::max(p->max_rows, sl.rows);
-    }
-    p->big_scatter = m1_big_scatter_lds(p->max_cols, p->max_rows) <= p->max_lds;
-  }
   if (p->fused && (rc = upload(&p->d_slots, p->h_slots)) != TN_OK) return rc;
   // The scatter's order of slots: the largest first, the small ones (one wave
   // per sample: few entries of a tensor of few hash words) last.
@@ -319,10 +332,6 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   if ((rc = upload(&p->d_sorted, sorted)) != TN_OK) return rc;
   if ((rc = upload(&p->d_tslot, p->h_tslot)) != TN_OK) return rc;
   if ((rc = upload(&p->d_nets, p->h_nets)) != TN_OK) return rc;
-  if ((rc = dev_alloc(&p->d_tables, (size_t)table_samples * (size_t)p->W)) != TN_OK) return rc;
-  unsigned char *yb = nullptr;
-  if ((rc = dev_alloc(&yb, (size_t)chunk * p->h_slots.size() * (size_t)p->m * as)) != TN_OK) return rc;
-  p->d_ybuf = yb;
   if ((rc = dev_alloc(&p->d_slot_bound, p->h_slots.size())) != TN_OK) return rc;
   if (p->two_pass) {
     // the tensors of each network two by two (an odd one out alone); with
@@ -344,32 +353,57 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     p->n_pairs = (int64_t)pairs.size() / 2;
     if ((rc = upload(&p->d_pairs, pairs)) != TN_OK) return rc;
     if ((rc = upload(&p->d_pair0, pair0)) != TN_OK) return rc;
-    unsigned char *cb = nullptr;
-    if ((rc = dev_alloc(&cb, (size_t)chunk * (size_t)p->n_pairs * (size_t)p->m * 2 * as)) != TN_OK) return rc;
-    p->d_cbuf = cb;
-    if ((rc = dev_alloc(&p->d_partial, (size_t)chunk * (size_t)p->n_nets * kBigPartials)) != TN_OK) return rc;
   }
-  // In-LDS combine with too few (network, sample) blocks to fill the GPU (one
-  // network with many tensors, as the ladder): each (network, sample) takes
-  // csplit blocks, each the product over a share of the tensor pairs, and a
-  // join kernel multiplies the partial spectra.
-  p->csplit = 1;
-  if (!p->two_pass && !p->fused && !(p->flags & (TN_FLAG_DFT_BF16 | TN_FLAG_DFT_FP8))) {
-    int64_t max_pairs = 0;
-    for (const NetDesc &nd : p->h_nets) max_pairs = std::max<int64_t>(max_pairs, (nd.t1 - nd.t0 + 1) / 2);
-    const int64_t blocks = (int64_t)p->n_nets * p->chunk_alloc;
-    // (only for long products: the join is one more launch, which small
-    // networks, launch-bound, do not repay)
-    if (blocks > 0 && blocks < kCombineSplitBlocks / 2 && max_pairs >= 2 && max_pairs * p->m >= kCombineSplitWork) {
-      const size_t H = (size_t)p->m / 2 + 1;
-      int64_t gs = std::min<int64_t>({(kCombineSplitBlocks + blocks - 1) / blocks, max_pairs, 64});
-      while (gs > 1 && (size_t)blocks * (size_t)gs * H * 16 > kCombineSplitBudget) --gs;
-      if (gs > 1) {
-        if ((rc = dev_alloc(&p->d_csplit, (size_t)blocks * (size_t)gs * H * 2)) != TN_OK) return rc;
-        p->csplit = (int32_t)gs;
+  // The workspace of a pass.
+  auto workspace = [&]() -> int {
+    int rc1;
+    const int64_t table_samples = std::max(p->chunk, p->fused_chunk_cap);
+    if ((rc1 = dev_alloc(&p->d_tables, (size_t)table_samples * (size_t)p->W)) != TN_OK) return rc1;
+    unsigned char *yb = nullptr, *cb = nullptr;
+    rc1 = dev_alloc(&yb, (size_t)p->chunk * sketch_bytes);
+    p->d_ybuf = yb;
+    if (rc1 != TN_OK) return rc1;
+    if (p->two_pass) {
+      rc1 = dev_alloc(&cb, (size_t)p->chunk * (size_t)p->n_pairs * (size_t)p->m * 2 * as);
+      p->d_cbuf = cb;
+      if (rc1 != TN_OK) return rc1;
+      if ((rc1 = dev_alloc(&p->d_partial, (size_t)p->chunk * (size_t)p->n_nets * kBigPartials)) != TN_OK) return rc1;
+    }
+    // In-LDS combine with too few (network, sample) blocks to fill the GPU (one
+    // network with many tensors, as the ladder): each (network, sample) takes
+    // csplit blocks, each the product over a share of the tensor pairs, and a
+    // join kernel multiplies the partial spectra.
+    p->csplit = 1;
+    if (!p->two_pass && !p->fused && !(p->flags & (TN_FLAG_DFT_BF16 | TN_FLAG_DFT_FP8))) {
+      int64_t max_pairs = 0;
+      for (const NetDesc &nd : p->h_nets) max_pairs = std::max<int64_t>(max_pairs, (nd.t1 - nd.t0 + 1) / 2);
+      const int64_t blocks = (int64_t)p->n_nets * p->chunk_alloc;
+      // (only for long products: the join is one more launch, which small
+      // networks, launch-bound, do not repay)
+      if (blocks > 0 && blocks < kCombineSplitBlocks / 2 && max_pairs >= 2 && max_pairs * p->m >= kCombineSplitWork) {
+        const size_t H = (size_t)p->m / 2 + 1;
+        int64_t gs = std::min<int64_t>({(kCombineSplitBlocks + blocks - 1) / blocks, max_pairs, 64});
+        while (gs > 1 && (size_t)blocks * (size_t)gs * H * 16 > kCombineSplitBudget) --gs;
+        if (gs > 1) {
+          if ((rc1 = dev_alloc(&p->d_csplit, (size_t)blocks * (size_t)gs * H * 2)) != TN_OK) return rc1;
+          p->csplit = (int32_t)gs;
+        }
       }
     }
+    return TN_OK;
+  };
+  rc = workspace();
+  if (rc == TN_ERR_OOM && budget > kWorkspaceBudget && !(p->flags & TN_FLAG_RESIDENT)) {
+    for (void *q : {(void *)p->d_tables, (void *)p->d_ybuf, p->d_cbuf, (void *)p->d_partial, (void *)p->d_csplit})
+      if (q) (void)hipFree(q);
+    p->d_tables = nullptr;
+    p->d_ybuf = p->d_cbuf = nullptr;
+    p->d_partial = p->d_csplit = nullptr;
+    clear_error();
+    set_chunk(kWorkspaceBudget);
+    rc = workspace();
   }
+  if (rc != TN_OK) return rc;
   if (p->m >= 2) {
     unsigned char *tw = nullptr;
     if ((rc = dev_alloc(&tw, (size_t)(p->m / 2) * 2 * as)) != TN_OK) return rc;
