@@ -89,6 +89,7 @@ struct tn_plan {
   int banks = 1;            // scatter accumulator banks (autotuned: 1 or 2)
   int64_t chunk = 0;        // samples per workspace pass
   int64_t chunk_alloc = 0;  // samples the workspace was sized for
+  int64_t y_chunk = 0;      // samples that d_ybuf holds (chunk, or fewer with big_scatter)
   size_t worst_cols_rows = 0;
   bool tuned = false;
   bool tables_ready = false;  // d_tables holds every sample's tables (resident plans)

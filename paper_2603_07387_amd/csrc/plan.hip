@@ -24,6 +24,7 @@ constexpr int kMaxRowsPerSlot = 2048;
 // 1.27, 1.48, 1.28), one otherwise and where that much cannot be had: a program
 // of many plans keeps room for them.
 constexpr size_t kWorkspaceBudget = (size_t)1 << 30, kWorkspaceLarge = (size_t)2 << 30;
+constexpr size_t kExportBudget = (size_t)256 << 20;   // sketches of a plan whose estimates do not keep them
 constexpr int64_t kScatterFill = 256;  // scatter blocks to keep (one per CU) when taking more samples per pass
 constexpr int64_t kCombineSplitBlocks = 1024;            // combine blocks to aim for when splitting
 constexpr size_t kCombineSplitBudget = (size_t)256 << 20;  // bytes of partial spectra
@@ -234,7 +235,8 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
 
   // m >= 2^15, FP32 sketches, every tensor one slot, and its words in the LDS
   // beside the transforms: the scatter takes the combine's first pass too
-  // (resident plans keep the sketches themselves).
+  // (resident plans keep the sketches themselves).  Only exported sketches
+  // then need memory, a few samples' at a time.
   if (p->two_pass && p->dtype != TN_F64 && !(p->flags & TN_FLAG_RESIDENT) &&
       p->h_slots.size() + 1 == p->h_tslot.size()) {
     for (const ScatterSlot &sl : p->h_slots) {
@@ -244,7 +246,7 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     p->big_scatter = m1_big_scatter_lds(p->max_cols, p->max_rows) <= p->max_lds;
   }
   const size_t sketch_bytes = p->h_slots.size() * (size_t)p->m * as;
-  const size_t per_sample = (size_t)p->W * 4 + sketch_bytes +
+  const size_t per_sample = (size_t)p->W * 4 + (p->big_scatter ? 0 : sketch_bytes) +
                             (p->two_pass ? (size_t)(p->n_tensors + p->n_nets) / 2 * (size_t)p->m * 2 * as +
                                                (size_t)p->n_nets * kBigPartials * 8
                                          : 0);
@@ -260,6 +262,9 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     p->chunk_alloc = chunk;
     if (chunk > 16 && !(p->flags & TN_FLAG_RESIDENT)) chunk = chunk / 16 * 16;  // a multiple of every samples-per-pass choice
     p->chunk = chunk;
+    p->y_chunk = !p->big_scatter
+                     ? chunk
+                     : std::min<int64_t>(chunk, std::max<int64_t>(1, (int64_t)(kExportBudget / sketch_bytes)));
   };
   size_t budget = kWorkspaceBudget;
   if (const char *env = getenv("TN_WORKSPACE_MB")) {  // (tests)
@@ -360,7 +365,7 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     const int64_t table_samples = std::max(p->chunk, p->fused_chunk_cap);
     if ((rc1 = dev_alloc(&p->d_tables, (size_t)table_samples * (size_t)p->W)) != TN_OK) return rc1;
     unsigned char *yb = nullptr, *cb = nullptr;
-    rc1 = dev_alloc(&yb, (size_t)p->chunk * sketch_bytes);
+    rc1 = dev_alloc(&yb, (size_t)p->y_chunk * sketch_bytes);
     p->d_ybuf = yb;
     if (rc1 != TN_OK) return rc1;
     if (p->two_pass) {
@@ -1057,8 +1062,8 @@ int plan_get_sketches(tn_plan *p, const tn_network *nets, int64_t first, int64_t
   if (rc != TN_OK) return rc;
   if (p->method == TN_ACYCLIC) return m2_get_sketches(p, first, count, st, out);
   if (p->partial && (rc = partial_prepare(p, st)) != TN_OK) return rc;
-  for (int64_t c0 = first; c0 < first + count; c0 += p->chunk) {
-    const int64_t n = std::min(p->chunk, first + count - c0);
+  for (int64_t c0 = first; c0 < first + count; c0 += p->y_chunk) {
+    const int64_t n = std::min(p->y_chunk, first + count - c0);
     const int32_t *tables = nullptr;
     if ((rc = m1_tables(p, c0, n, st, &tables)) != TN_OK) return rc;
     M1Launch L{};

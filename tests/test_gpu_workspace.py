@@ -57,6 +57,21 @@ def test_passes(case, monkeypatch):
     assert np.array_equal(plan.sketches(0, S).cpu().numpy(), whole.sketches(0, S).cpu().numpy())
 
 
+def test_unused_sketches_take_no_room(monkeypatch):
+    """9 tensors, m = 65536: 2.4 MB of sketches and 2.6 MB of transforms per sample; estimates keep the latter only.
+    Exported sketches come in several pieces."""
+    import paper_2603_07387_amd as T
+    net = W.torus(L=3, D=8, seed=6, dist="normal")
+    monkeypatch.setenv("TN_WORKSPACE_MB", "64")
+    plan, _ = make(T, [net], 65536, 30, "float32")
+    assert plan.query(9) >= 16
+    monkeypatch.delenv("TN_WORKSPACE_MB")
+    plan, _ = make(T, [net], 65536, 130, "float32")
+    whole, _ = make(T, [net], 65536, 130, "float32", flags=T.TN_FLAG_RESIDENT)
+    for first, count in ((0, 130), (100, 30), (129, 1)):
+        assert np.array_equal(plan.sketches(first, count).cpu().numpy(), whole.sketches(first, count).cpu().numpy())
+
+
 def test_smaller_workspace_after_out_of_memory(monkeypatch):
     """A workspace that the device does not have (537 GB of sketches): the plan takes one of 1 GiB instead."""
     import paper_2603_07387_amd as T
