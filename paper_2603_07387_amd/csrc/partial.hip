@@ -86,9 +86,12 @@ int upload_p(T **ptr, const std::vector<T> &v) {
 // the smaller group.  A 3 x 3 torus of bond 8 with two contractions cut (4096
 // entries, 20480 transforms per sample), 8 samples of m = 1024, FP32: 444 us
 // per call singly, 72 with groups of 512 and 8 assignments (544 transforms).
-// Taken where it at least halves the transforms and the single way's blocks,
-// one per entry and sample, would be more than run at once (m = 256, single /
-// grouped: 28.3 / 29.3 us for 1024 of them, 34.0 / 30.2 for 2048); the split
+// Taken where it at least halves the transforms, with their spectra's way through
+// memory counted as another each (2 x 2 entries of three tensors, 526 samples, m =
+// 1024, which are left: 49.8 us singly, 67 grouped), and where the single way's
+// blocks, one per entry and sample, would be more than run at once (m = 256,
+// single / grouped: 28.3 / 29.3 us for 1024 of them, 34.0 / 30.2 for 2048; at m =
+// 8192 the line is low: 488 us singly for 1792, 162 grouped for 2048); the split
 // combine and the matrix-core transforms have no form that leaves a pair's
 // spectrum.  cbeg, cend: the slots of the assignments' tensors; group_n stays
 // 0 if the entries are taken singly.
@@ -126,7 +129,7 @@ int group_build(tn_plan *p, int np, std::vector<int32_t> *cbeg, std::vector<int3
   }
   const int big = count[0] >= count[1] ? 0 : 1;
   const int64_t transforms = count[0] * (int64_t)group[0].size() + count[1] * (int64_t)group[1].size();
-  if (2 * transforms > p->n_out * pairs) return TN_OK;
+  if (2 * transforms > p->n_out * pairs || transforms + count[0] + count[1] >= p->n_out * pairs) return TN_OK;
   const size_t per_sample = (size_t)(count[0] + count[1]) * ((size_t)p->m / 2 + 1) * 16;
   const int64_t chunk = std::min<int64_t>(p->chunk_alloc, (int64_t)(kGroupBudget / per_sample));
   if (chunk < 1) return TN_OK;
