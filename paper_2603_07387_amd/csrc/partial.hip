@@ -303,6 +303,14 @@ int partial_build(tn_plan *p, const tn_network *net) {
   p->h_nets.clear();
   for (int64_t r = 0; r < n_out; ++r) p->h_nets.push_back(NetDesc{(int32_t)(r * n.p), (int32_t)((r + 1) * n.p)});
   if ((rc = m1_layout(p, nullptr)) != TN_OK) return rc;  // completes h_tslot with its end sentinel
+  if (n_perm > 0) {
+    unsigned char *buf = nullptr;
+    if ((rc = dev_alloc_p(&buf, (size_t)perm_bytes)) != TN_OK) return rc;
+    p->d_perm = buf;
+    if ((rc = dev_alloc_p(&p->d_psrc, (size_t)n_perm)) != TN_OK) return rc;
+    p->psrc.assign((size_t)n_perm, nullptr);
+  }
+  // (last of the large allocations: without room for its spectra the entries are taken singly)
   std::vector<int32_t> cbeg, cend;
   if ((rc = group_build(p, n.p, &cbeg, &cend)) != TN_OK) return rc;
   if (p->group_n[0] == 0) {
@@ -329,13 +337,6 @@ int partial_build(tn_plan *p, const tn_network *net) {
   }
   if ((rc = upload_p(&p->d_cbeg, cbeg)) != TN_OK) return rc;
   if ((rc = upload_p(&p->d_cend, cend)) != TN_OK) return rc;
-  if (n_perm > 0) {
-    unsigned char *buf = nullptr;
-    if ((rc = dev_alloc_p(&buf, (size_t)perm_bytes)) != TN_OK) return rc;
-    p->d_perm = buf;
-    if ((rc = dev_alloc_p(&p->d_psrc, (size_t)n_perm)) != TN_OK) return rc;
-    p->psrc.assign((size_t)n_perm, nullptr);
-  }
   return TN_OK;
 }
 
