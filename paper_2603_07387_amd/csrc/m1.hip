@@ -485,7 +485,8 @@ template <typename T, typename A>
 __global__ __launch_bounds__(256) void m1_scatter_small_kernel(
     const ScatterSlot *__restrict__ slots, int32_t n, const ModeDesc *__restrict__ modes,
     const void *const *__restrict__ data, const int32_t *__restrict__ tables, int64_t W, int64_t samples,
-    int log2m, int64_t n_slots, A *__restrict__ ybuf, int32_t gs, int32_t groups, int32_t gx) {
+    int log2m, int64_t n_slots, A *__restrict__ ybuf, double *__restrict__ bound_out, int32_t gs, int32_t groups,
+    int32_t gx) {
   constexpr int K = kSmallSlot / 64, KW = kStageWords / 64;
   static_assert(kStageWords <= 255 && kStageWords % 64 == 0, "word positions are packed in bytes");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -568,6 +569,7 @@ __global__ __launch_bounds__(256) void m1_scatter_small_kernel(
     (void)frexp(lmax, &e);  // max|x| < 2^e
     scale = 62 - 11 - e;    // N <= 2^11 (see m1_scatter_kernel)
   }
+  if (bound_out != nullptr && grp == 0 && threadIdx.x == 0) bound_out[sl.pad] = lmax > 0.0 ? ldexp(1.0, 51 - scale - 1) : 0.0;
   const double sc = ldexp(1.0, scale);
   constexpr double kMagic = 6755399441055744.0;
   const long long kMagicBits = __double_as_longlong(kMagic);
@@ -655,11 +657,17 @@ __device__ __forceinline__ void sum_as_256(double term, int64_t j0, int64_t H, d
 // ranges: entry k's sketch is the sum of the slots [tbeg[k], tend[k]) (a
 // plan's tensors in order: tbeg = first slot of each tensor, tend = tbeg + 1;
 // a partial plan lists each entry's, or each group entry's, sub-tensors).
-template <typename A, int LOG2M, bool TWL, int NTH = 256>
+// SCALED (group entries): every tensor is scaled by the power of two up to its
+// largest entry (bound), pexp their exponents' sum, so that the product of a group's
+// tensors, which are not neighbours in the network, neither overflows nor
+// vanishes where the whole product does not.  Exact: the spectra's bits are those
+// of the plain product, their exponents apart.
+template <typename A, int LOG2M, bool TWL, int NTH, bool SCALED>
 __global__ __launch_bounds__(NTH) void m1_combine_kernel(
     const NetDesc *__restrict__ nets, const int32_t *__restrict__ tbeg, const int32_t *__restrict__ tend,
     const A *__restrict__ ybuf, int64_t n_slots, int64_t sample0, int64_t S,
-    const typename Cplx<A>::type *__restrict__ tw, double *__restrict__ est, double2 *__restrict__ part) {
+    const typename Cplx<A>::type *__restrict__ tw, double *__restrict__ est, double2 *__restrict__ part,
+    const double *__restrict__ bound, int32_t *__restrict__ pexp) {
   using A2 = typename Cplx<A>::type;
   constexpr int M = 1 << LOG2M;
   constexpr int H = M / 2 + 1;
@@ -698,6 +706,14 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
   double pr[NC], pi[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) { pr[c] = 1.0; pi[c] = 0.0; }
+  int esum = 0;
+  // Largest power of two up to any entry of the slots [from, to).  (The first
+  // load is not waited for where there is one slot.)
+  auto largest = [&](int from, int to) {
+    double b = bound[from];
+    for (int sl = from + 1; sl < to; ++sl) b = fmax(b, bound[sl]);
+    return b;
+  };
 
   // With one load round per pair (M <= NTH G), the first slot of each tensor
   // of the next pair is loaded before this pair's transform: the loads stay
@@ -751,6 +767,11 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
     // slots [a0, a1) of the first tensor of the pair, [b0, b1) of the second
     const int a0 = tbeg[k], a1 = tend[k];
     const int b0 = pair ? tbeg[k + 1] : 0, b1 = pair ? tend[k + 1] : 0;
+    double ba = 1.0, bb = 1.0;
+    if constexpr (SCALED) {
+      ba = largest(a0, a1);
+      if (pair) bb = largest(b0, b1);
+    }
     if constexpr (ONE_ROUND) {
       A v1[G], v2[G];
 #pragma unroll
@@ -782,6 +803,13 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
       fft_lds<A, LOG2M, true, NTH>(z, t);
     else
       fft_lds_tw<A, LOG2M, true, NTH>(z, Tw2<A>{t, t + M / 128});
+    double half = 0.5, quarter = 0.25;
+    if constexpr (SCALED) {
+      const int ek = min(max((ba > 0.0 ? ilogb(ba) : 0) + (bb > 0.0 ? ilogb(bb) : 0), -1000), 1000);
+      esum += ek;
+      half = ldexp(0.5, -ek);
+      quarter = ldexp(0.25, -ek);
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int j = tid + NTH * c;
@@ -792,11 +820,11 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
         if (pair) {
           const double dr = (ar * ar - ai * ai) - (br * br - bi * bi);
           const double di = 2.0 * (ar * ai - br * bi);
-          qr = 0.25 * di;     // -i (A^2 - B^2) / 4
-          qi = -0.25 * dr;
+          qr = quarter * di;     // -i (A^2 - B^2) / 4
+          qi = -quarter * dr;
         } else {
-          qr = 0.5 * (ar + br);  // (A + B) / 2
-          qi = 0.5 * (ai + bi);
+          qr = half * (ar + br);  // (A + B) / 2
+          qi = half * (ai + bi);
         }
         times(pr[c], pi[c], qr, qi);
       }
@@ -811,6 +839,7 @@ __global__ __launch_bounds__(NTH) void m1_combine_kernel(
       const int j = tid + NTH * c;
       if (j < H) o[j] = make_double2(pr[c], pi[c]);
     }
+    if (SCALED && s == 0 && tid == 0) pexp[blockIdx.x] = esum;
     return;
   }
   double sum = 0.0;
@@ -864,7 +893,7 @@ __global__ __launch_bounds__(kJoinThreads) void m1_combine_join_kernel(const dou
 
 // All entries of a partial contraction from the product spectra of two groups
 // of its tensor pairs: entry loff[a] + roff[b] of sample s is
-// (1/m) sum_j w_j Re(L_a[j] R_b[j]), L_a = spec[a][s], R_b = spec[nl + b][s],
+// (with pexp: 2^(pexp[a] + pexp[nl + b]) times) (1/m) sum_j w_j Re(L_a[j] R_b[j]), L_a = spec[a][s], R_b = spec[nl + b][s],
 // w_j = 1 at j = 0 and m/2, else 2: a real product of depth m + 2, taken on
 // v_mfma_f64_16x16x4f64 (A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
 // D[i][j] element i / 4 of lane j + 16 (i % 4)).  A block owns a 16 x 16 tile
@@ -875,8 +904,8 @@ __global__ __launch_bounds__(kJoinThreads) void m1_combine_join_kernel(const dou
 constexpr int kOuterLoads = 8;
 __global__ __launch_bounds__(256) void m1_outer_kernel(const double2 *__restrict__ spec, int32_t nl, int32_t nr,
                                                        const int32_t *__restrict__ loff,
-                                                       const int32_t *__restrict__ roff, int64_t m,
-                                                       int64_t sample0, int64_t S, double *__restrict__ est) {
+                                                       const int32_t *__restrict__ roff,
+                                                       const int32_t *__restrict__ pexp, int64_t m, int64_t sample0, int64_t S, double *__restrict__ est) {
   typedef double f64x4 __attribute__((ext_vector_type(4)));
   __shared__ double sums[3][64][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -884,6 +913,12 @@ __global__ __launch_bounds__(256) void m1_outer_kernel(const double2 *__restrict
   const int64_t s = blockIdx.z, n = gridDim.z, H = m / 2 + 1;
   const double2 *pa = spec + ((int64_t)min(a0 + (lane & 15), nl - 1) * n + s) * H;
   const double2 *pb = spec + ((int64_t)(nl + min(b0 + (lane & 15), nr - 1)) * n + s) * H;
+  const int b = b0 + (lane & 15);
+  int ex[4] = {0, 0, 0, 0};
+  if (pexp != nullptr) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ex[i] = pexp[min(a0 + 4 * i + (lane >> 4), nl - 1)] + pexp[nl + min(b, nr - 1)];
+  }
   f64x4 acc = {0.0, 0.0, 0.0, 0.0};
   for (int64_t j0 = 4 * wave; j0 < H; j0 += 16 * kOuterLoads) {
     double2 va[kOuterLoads], vb[kOuterLoads];
@@ -908,12 +943,12 @@ __global__ __launch_bounds__(256) void m1_outer_kernel(const double2 *__restrict
   }
   __syncthreads();
   if (wave > 0) return;
-  const int b = b0 + (lane & 15);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int a = a0 + 4 * i + (lane >> 4);
     const double v = ((acc[i] + sums[0][lane][i]) + sums[1][lane][i]) + sums[2][lane][i];
-    if (a < nl && b < nr) est[(int64_t)(loff[a] + roff[b]) * S + sample0 + s] = v / (double)m;
+    if (a < nl && b < nr)
+      est[(int64_t)(loff[a] + roff[b]) * S + sample0 + s] = ldexp(v / (double)m, ex[i]);
   }
 }
 
@@ -1577,8 +1612,8 @@ int scatter_sb(const M1Launch &L, hipStream_t st) {
     TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   const dim3 grid(slot_blocks((uint32_t)n, (uint32_t)gx), (unsigned)((groups + gx - 1) / gx));
   hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, L.slots + L.n_big, (int32_t)n, L.modes, L.data, L.tables, L.W,
-                     L.samples, L.log2m, L.n_slots, reinterpret_cast<A *>(L.ybuf), (int32_t)gs,
-                     (int32_t)groups, (int32_t)gx);
+                     L.samples, L.log2m, L.n_slots, reinterpret_cast<A *>(L.ybuf),
+                     L.record_bound ? L.slot_bound : nullptr, (int32_t)gs, (int32_t)groups, (int32_t)gx);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }
@@ -1598,7 +1633,7 @@ constexpr int64_t kFewCombineBlocks = 256;
 template <typename A, int LOG2M, int NTH = LOG2M >= 13 ? 1024 : 256>
 int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend, const void *ybuf,
               int64_t n_slots, int64_t samples, int64_t sample0, int64_t S, const void *tw,
-              double *est, int32_t csplit, double *cpart, hipStream_t st) {
+              double *est, int32_t csplit, double *cpart, const double *bound, int32_t *pexp, hipStream_t st) {
   using A2 = typename Cplx<A>::type;
   // z (m points, one spare element per 32: bank spread) and, when the total
   // stays within 64 KB, the m/2 twiddles (padded), else the two-level table
@@ -1616,8 +1651,8 @@ int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
     if constexpr (LOG2M >= 11 && NTH == 256)
       if (blocks <= kFewCombineBlocks)
         return combine_m<A, LOG2M, 1024>(nets, n_nets, tbeg, tend, ybuf, n_slots, samples, sample0, S, tw, est, csplit,
-                                         cpart, st);
-    auto kern = m1_combine_kernel<A, LOG2M, TWL, NTH>;
+                                         cpart, bound, pexp, st);
+    auto kern = bound ? m1_combine_kernel<A, LOG2M, TWL, NTH, true> : m1_combine_kernel<A, LOG2M, TWL, NTH, false>;
     if (lds > 65536)
       TN_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds));
@@ -1626,7 +1661,7 @@ int combine_m(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
     double2 *part = reinterpret_cast<double2 *>(cpart);
     hipLaunchKernelGGL(kern, grid, dim3(NTH), lds, st, nets, tbeg, tend,
                        reinterpret_cast<const A *>(ybuf), n_slots, sample0, S,
-                       reinterpret_cast<const A2 *>(tw), est, part);
+                       reinterpret_cast<const A2 *>(tw), est, part, bound, pexp);
     TN_HIP_CHECK(hipGetLastError());
     if (split && est != nullptr) {
       hipLaunchKernelGGL(m1_combine_join_kernel, dim3((unsigned)n_nets, (unsigned)samples),
@@ -1671,11 +1706,12 @@ int combine_big(int64_t n_nets, const int32_t *tslot, const int32_t *pairs, cons
 template <typename A>
 int combine_t(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend, const void *ybuf,
               int64_t n_slots, int64_t samples, int64_t sample0, int64_t S, int log2m,
-              const void *tw, double *est, int32_t csplit, double *cpart, hipStream_t st) {
+              const void *tw, double *est, int32_t csplit, double *cpart, const double *bound, int32_t *pexp,
+              hipStream_t st) {
 #define TN_COMBINE_CASE(LG)                                                                            \
   case LG:                                                                                             \
     return combine_m<A, LG>(nets, n_nets, tbeg, tend, ybuf, n_slots, samples, sample0, S, tw, est, csplit, \
-                            cpart, st);
+                            cpart, bound, pexp, st);
   switch (log2m) {
     TN_COMBINE_CASE(0) TN_COMBINE_CASE(1) TN_COMBINE_CASE(2) TN_COMBINE_CASE(3)
     TN_COMBINE_CASE(4) TN_COMBINE_CASE(5) TN_COMBINE_CASE(6) TN_COMBINE_CASE(7)
@@ -1736,22 +1772,22 @@ int launch_m1_big_scatter(const M1Launch &L, const int32_t *pairs, int64_t n_pai
 int launch_m1_combine(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend, int dtype,
                       const void *ybuf, int64_t n_slots, int64_t samples, int64_t sample0,
                       int64_t S, int log2m, const void *tw, double *est, int32_t csplit, double *cpart,
-                      hipStream_t st) {
+                      hipStream_t st, const double *bound, int32_t *pexp) {
   if (n_nets == 0 || samples == 0) return TN_OK;
   if (samples > 65535) return set_error(TN_ERR_UNSUPPORTED, "combine: samples per launch");
   if (dtype == TN_F64)
     return combine_t<double>(nets, n_nets, tbeg, tend, ybuf, n_slots, samples, sample0, S, log2m, tw, est, csplit,
-                             cpart, st);
+                             cpart, bound, pexp, st);
   return combine_t<float>(nets, n_nets, tbeg, tend, ybuf, n_slots, samples, sample0, S, log2m, tw, est, csplit,
-                          cpart, st);
+                          cpart, bound, pexp, st);
 }
 
 int launch_m1_outer(const double *spec, int64_t nl, int64_t nr, const int32_t *loff, const int32_t *roff,
-                    int64_t samples, int64_t sample0, int64_t S, int64_t m, double *est, hipStream_t st) {
+                    const int32_t *pexp, int64_t samples, int64_t sample0, int64_t S, int64_t m, double *est, hipStream_t st) {
   if (samples > 65535 || nr > 16 * 65535) return set_error(TN_ERR_UNSUPPORTED, "outer product: grid");
   const dim3 grid((unsigned)((nl + 15) / 16), (unsigned)((nr + 15) / 16), (unsigned)samples);
   hipLaunchKernelGGL(m1_outer_kernel, grid, dim3(256), 0, st, reinterpret_cast<const double2 *>(spec), (int32_t)nl,
-                     (int32_t)nr, loff, roff, m, sample0, S, est);
+                     (int32_t)nr, loff, roff, pexp, m, sample0, S, est);
   TN_HIP_CHECK(hipGetLastError());
   return TN_OK;
 }

@@ -158,6 +158,10 @@ int group_build(tn_plan *p, int np, std::vector<int32_t> *cbeg, std::vector<int3
   }
   int rc = upload_p(&p->d_gnets, nets);
   if (rc == TN_OK) rc = upload_p(&p->d_goff, goff);
+  // FP32 sketches are below 2^128, their spectra's products of up to three pairs
+  // within the range of FP64 either way: only others are scaled
+  if (rc == TN_OK && (p->dtype == TN_F64 || std::max(group[0].size(), group[1].size()) > 3))
+    rc = dev_alloc_p(&p->d_gexp, nets.size());
   if (rc == TN_OK) rc = dev_alloc_p(&p->d_gspec, (size_t)chunk * per_sample / 8);
   if (rc == TN_ERR_OOM) {  // no room for the spectra: the entries singly
     clear_error();
@@ -182,9 +186,9 @@ int partial_combine(tn_plan *p, int64_t samples, int64_t sample0, double *est, h
     const unsigned char *y =
         reinterpret_cast<const unsigned char *>(p->d_ybuf) + (size_t)(s0 * n_slots * p->m) * as;
     int rc = launch_m1_combine(p->d_gnets, nl + nr, p->d_cbeg, p->d_cend, p->dtype, y, n_slots, n, sample0 + s0, p->S,
-                               p->log2m, p->d_tw, nullptr, 1, p->d_gspec, st);
+                               p->log2m, p->d_tw, nullptr, 1, p->d_gspec, st, p->d_gexp ? p->d_slot_bound : nullptr, p->d_gexp);
     if (rc != TN_OK) return rc;
-    if ((rc = launch_m1_outer(p->d_gspec, nl, nr, p->d_goff, p->d_goff + nl, n, sample0 + s0, p->S, p->m, est, st)) !=
+    if ((rc = launch_m1_outer(p->d_gspec, nl, nr, p->d_goff, p->d_goff + nl, p->d_gexp, n, sample0 + s0, p->S, p->m, est, st)) !=
         TN_OK)
       return rc;
   }
@@ -418,12 +422,12 @@ int partial_prepare(tn_plan *p, hipStream_t st) {
 }
 
 void partial_release(tn_plan *p) {
-  void *ptrs[] = {p->d_perm, (void *)p->d_psrc, p->d_cbeg, p->d_cend, p->d_gnets, p->d_goff, p->d_gspec};
+  void *ptrs[] = {p->d_perm, (void *)p->d_psrc, p->d_cbeg, p->d_cend, p->d_gnets, p->d_goff, p->d_gexp, p->d_gspec};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   p->d_perm = nullptr;
   p->d_psrc = nullptr;
-  p->d_cbeg = p->d_cend = p->d_goff = nullptr;
+  p->d_cbeg = p->d_cend = p->d_goff = p->d_gexp = nullptr;
   p->d_gnets = nullptr;
   p->d_gspec = nullptr;
 }

@@ -141,6 +141,7 @@ struct tn_plan {
   int64_t group_chunk = 0;      // samples that d_gspec holds
   tn::NetDesc *d_gnets = nullptr;
   int32_t *d_goff = nullptr;    // [sum of group_n]: each assignment's part of the entry's index
+  int32_t *d_gexp = nullptr;    // exponent of the power of two taken out of each assignment's spectra
   double *d_gspec = nullptr;
 
   // acyclic method

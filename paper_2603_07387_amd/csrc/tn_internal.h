@@ -172,11 +172,12 @@ int launch_m1_big_scatter(const M1Launch &L, const int32_t *pairs, int64_t n_pai
 int launch_m1_combine(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend,
                       int dtype, const void *ybuf, int64_t n_slots, int64_t samples,
                       int64_t sample0, int64_t S, int log2m, const void *twiddles,
-                      double *est, int32_t csplit, double *cpart, hipStream_t st);
+                      double *est, int32_t csplit, double *cpart, hipStream_t st,
+                      const double *slot_bound = nullptr, int32_t *pexp = nullptr);
 // A partial contraction's entries from the spectra of its two groups
 // (spec[nl + nr][samples][m/2 + 1], complex): entry loff[a] + roff[b].
 int launch_m1_outer(const double *spec, int64_t nl, int64_t nr, const int32_t *loff, const int32_t *roff,
-                    int64_t samples, int64_t sample0, int64_t S, int64_t m, double *est, hipStream_t st);
+                    const int32_t *pexp, int64_t samples, int64_t sample0, int64_t S, int64_t m, double *est, hipStream_t st);
 // The combine with its 1024-point DFTs on the BF16 matrix cores, or with fp8
 // on the FP8 ones (dft.hip; FP32 sketches, m = 1024 only).
 int launch_m1_combine_dft32(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const int32_t *tend,
