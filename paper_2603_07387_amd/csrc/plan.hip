@@ -269,7 +269,7 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
   size_t budget = kWorkspaceBudget;
   if (const char *env = getenv("TN_WORKSPACE_MB")) {  // (tests)
     budget = (size_t)std::max(1ll, atoll(env)) << 20;
-  } else {
+  } else if ((double)per_sample * (double)p->S > (double)budget) {  // (the query takes 10 us)
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) (void)hipGetLastError();
     else if (free_b / 3 >= total_b / 4) budget = kWorkspaceLarge;
