@@ -76,7 +76,7 @@ __device__ __forceinline__ void load_row(const uint32_t *p, uint32_t *out) {
 // the rows t / V + k (NT / V).  Its SB x 4 column words are held in registers
 // for a batch, no term divides or tests a row end, and a vector reads only its
 // row's SB words from LDS (rowt, one 16-byte broadcast read for four samples),
-// a chunk of kRowChunk rows at a time.
+// row_chunk(SB) rows at a time.
 // A term is then one add, one and-or and the LDS atomic with BANKS = 2:
 // sketches are pairs of banks of m words, +1 terms in the positive bank, -1
 // terms in the negative one, the sketch their difference.  Sample s's positive
@@ -123,6 +123,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
     const void *const *__restrict__ data, const int32_t *__restrict__ tables, int64_t W, int64_t samples,
     int log2m, int64_t n_slots, A *__restrict__ ybuf, const double *__restrict__ bound_in,
     double *__restrict__ bound_out, int32_t gs, int32_t groups, int32_t gx, int32_t rsplit) {
+  constexpr int kRows = row_chunk(SB);  // rows whose words are in the LDS at a time
   static_assert(!RANGED || (BANKS == 1 && SB == 1), "bucket ranges use one bank and one sample");
   using Q = typename Quad<T>::type;
   constexpr int U = BANKS == 1 || SB * sizeof(T) >= 32 ? 2 : 4;  // row vectors in flight per thread
@@ -143,8 +144,8 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
   const uint32_t acc_bytes = BANKS == 2 ? (uint32_t)sign_bank_bytes(SB, m) : (uint32_t)SB * 8u * ma;
   const uint32_t acc_end = (acc_bytes + 15u) & ~15u;
   unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem);
-  uint32_t *rowt = reinterpret_cast<uint32_t *>(smem + acc_end);  // [kRowChunk][SB]
-  uint32_t *stage = rowt + kRowChunk * SB;                        // [kStageWords][SB]
+  uint32_t *rowt = reinterpret_cast<uint32_t *>(smem + acc_end);  // [kRows][SB]
+  uint32_t *stage = rowt + kRows * SB;                        // [kStageWords][SB]
   unsigned long long *s_max = reinterpret_cast<unsigned long long *>(stage + kStageWords * SB);
   const int L = sl.L, rows = sl.rows;
   const T __attribute__((address_space(1))) *X =
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
   // Few rows and columns: the column words too are formed once per block, after
   // the row words, instead of by every thread for its own columns (64 triangles
   // of 64 x 64, 256 samples, m = 256, FP64: 205 -> 188 us per call).
-  const bool few = rows + L <= kRowChunk;
+  const bool few = rows + L <= kFewWords;
   lds_zero(acc, acc_bytes, tid, NT);
   put(grp * gs);
   for (int32_t batch = grp * gs; batch < batch_end; ++batch) {
@@ -348,10 +349,10 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
     const int range0 = RANGED ? run - grp * rsplit : 0;
     for (int range = range0; range < nranges; range += rstep) {
       const uint32_t rlo = (uint32_t)range << (3 + log2acc), rlen = 8u << log2acc;
-      for (int rb = 0; rb < rows; rb += kRowChunk) {
-        const int re = min(rows, rb + kRowChunk);
+      for (int rb = 0; rb < rows; rb += kRows) {
+        const int re = min(rows, rb + kRows);
         if (rb > 0) __syncthreads();  // the last chunk's readers are done
-        if (range == range0 || rows > kRowChunk) {
+        if (range == range0 || rows > kRows) {
           // rows, then (few) columns
           for (int r = rb + tid; r < re + (few ? L : 0); r += NT) {
             uint32_t w[SB];
@@ -1727,7 +1728,7 @@ int combine_t(const NetDesc *nets, int64_t n_nets, const int32_t *tbeg, const in
 size_t m1_scatter_lds(int sb, int banks, int log2m) {
   const size_t ma = (size_t)1 << std::min(log2m, kMaxLog2Acc);  // bucket ranges above
   const size_t acc = banks == 2 ? sign_bank_bytes(sb, (uint32_t)ma) : (size_t)sb * 8 * ma;
-  return ((acc + 15) & ~(size_t)15) + (size_t)sb * 4 * (kRowChunk + kStageWords) + 16;
+  return ((acc + 15) & ~(size_t)15) + (size_t)sb * 4 * (row_chunk(sb) + kStageWords) + 16;
 }
 
 int launch_m1_scatter(const M1Launch &L, hipStream_t st) {

@@ -82,7 +82,10 @@ constexpr int kColPad = 8;              // words after each sample's column tabl
 constexpr int kMaxSlotEntries = 1 << 16;  // entries per scatter block
 constexpr int kMaxLog2M1 = 16;          // m <= 65536
 constexpr size_t kMaxLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
-constexpr int kRowChunk = 512;          // rows whose hash words a scatter block holds in LDS at a time
+// Rows whose hash words a scatter block of sb samples per pass holds in LDS at a
+// time.
+constexpr int row_chunk(int sb) { return sb == 1 ? 2048 : sb == 2 ? 1024 : 512; }
+constexpr int kFewWords = 512;          // rows and columns of a slot whose words are all formed together
 constexpr int kSmallSlot = 1024;        // entries of a slot that the scatter takes one wave per sample for
 constexpr int kMaxLog2Small = 11;       // largest log2 m of those (four waves' accumulators in a block's LDS)
 constexpr int kStageWords = 192;        // mode indices of a tensor whose hash words a scatter block stages
