@@ -214,13 +214,19 @@ typedef struct tn_plan tn_plan;
  *                  sample per pass; when the m-point FFT does not fit in LDS,
  *                  from 16384 with TN_F64 data and 32768 otherwise, the combine
  *                  runs in two passes through a device workspace of
- *                  tensors x m complex values per sample; when a launch has
+ *                  tensor pairs x m complex values per sample; when a launch has
  *                  under 512 (network, sample) pairs and a network's pairs of
  *                  tensors times m reach 65536, each (network, sample) is
  *                  combined by several blocks over shares of its pairs, with
  *                  a workspace of their m/2 + 1 complex products, at most
  *                  256 MB),
- *                  2 <= m <= 8192 for TN_ACYCLIC.
+ *                  2 <= m <= 8192 for TN_ACYCLIC.  A cyclic plan's samples go
+ *                  through a workspace of hash tables, sketches and such
+ *                  transforms in passes: at most 2 GiB while three quarters
+ *                  of the device's memory are free, else (and where that
+ *                  cannot be had) 1 GiB, or one sample's if that is more;
+ *                  partial plans add up to 256 MiB of spectra.  An acyclic
+ *                  plan's takes at most 2 GiB.
  *   samples      : S >= 1 independent sketch samples per network (S <= 0
  *                  only with m <= 0: chosen too); sample r
  *                  uses hash key (seed + j, r, stream) for network j.

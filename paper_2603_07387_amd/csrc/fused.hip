@@ -7,7 +7,7 @@
 // empty (every block reaches that exit).  For its item a block walks the
 // network's tensors two at a time:
 //   1. both tensors' slots are scattered into 64-bit fixed-point sketches in
-//      LDS (the same scatter as the slot kernel, one scale per tensor);
+//      LDS (scatter_slot, one scale per tensor, set by a running maximum);
 //   2. per sample, the two real sketches share one complex FFT in LDS
 //      (z = y_a + i y_b), and the pair's product spectrum
 //      Y_a Y_b = (Z[j]^2 - conj(Z[-j])^2) / 4i is multiplied into per-thread

@@ -7,10 +7,12 @@
 // estimate is e_1^T F^{-1}(F y_1 o ... o F y_p) = (1/m) sum_j prod_k Y_k[j].
 //
 // Kernels:
-//   m1_scatter  : one block streams one slot (a run of rows of one tensor)
-//                 once from HBM, coalesced, and accumulates the sketches of SB
-//                 samples in LDS in 64-bit fixed point (packed bucket/sign
-//                 tables in LDS too).
+//   m1_scatter  : one block takes one slot (a run of rows of one tensor), whose
+//                 entries it reads once for the largest and once per batch of
+//                 samples, and accumulates the sketches of SB samples at a time in
+//                 LDS in 64-bit fixed point; a wave per sample for small slots.
+//   m1_big_scatter: m >= 2^15, FP32 sketches: scatter and the combine's first
+//                 transforms in one, a pair of tensors' sketches by ranges.
 //   m1_combine  : one block per (network, sample): two real sketches share one
 //                 complex FFT in LDS (z = y_a + i y_b), the pair's product
 //                 spectrum Y_a Y_b = (Z[j]^2 - conj(Z[-j])^2) / 4i is folded into
@@ -111,7 +113,7 @@ __device__ __forceinline__ void load_row(const uint32_t *p, uint32_t *out) {
 // outside the current one; `rsplit` blocks share a group's ranges where the
 // groups are few.
 //
-// slots: in decreasing order of size (pad: the slot's number), so that the last
+// slots: in decreasing order of size (id: the slot's number), so that the last
 // blocks to start are short; their blocks as slot_block gives them.
 // Registers: six waves per SIMD (three blocks per CU) for 512-thread blocks with
 // one bank, whose LDS leaves room for them at m = 1024 (batch of 4096 networks:
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(NT, BANKS == 1 && NT == 512 && SB * sizeof(A) <= 16
   const int32_t grp = RANGED ? run / rsplit : run;
   if (pos >= n || grp >= groups) return;  // padding of the grid
   const ScatterSlot sl = slots[pos];
-  const int32_t sid = sl.pad;
+  const int32_t sid = sl.id;
   const int tid = threadIdx.x;
   const uint32_t m = 1u << log2m, mask = m - 1;
   constexpr int log2acc = kMaxLog2Acc;
@@ -570,7 +572,8 @@ __global__ __launch_bounds__(256) void m1_scatter_small_kernel(
     (void)frexp(lmax, &e);  // max|x| < 2^e
     scale = 62 - 11 - e;    // N <= 2^11 (see m1_scatter_kernel)
   }
-  if (bound_out != nullptr && grp == 0 && threadIdx.x == 0) bound_out[sl.pad] = lmax > 0.0 ? ldexp(1.0, 51 - scale - 1) : 0.0;
+  if (bound_out != nullptr && grp == 0 && threadIdx.x == 0)
+    bound_out[sl.id] = lmax > 0.0 ? ldexp(1.0, 50 - scale) : 0.0;  // 2^(e - 1)
   const double sc = ldexp(1.0, scale);
   constexpr double kMagic = 6755399441055744.0;
   const long long kMagicBits = __double_as_longlong(kMagic);
@@ -604,7 +607,7 @@ __global__ __launch_bounds__(256) void m1_scatter_small_kernel(
                                  (unsigned long long)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     fence();
-    A *dst = ybuf + (s * n_slots + sl.pad) * (int64_t)m;
+    A *dst = ybuf + (s * n_slots + sl.id) * (int64_t)m;
     auto value = [&](unsigned long long t) { return (A)ldexp((double)(long long)t, -scale); };
     if (log2m >= 2) {
       for (uint32_t i4 = lane; i4 < m / 4; i4 += 64) {
@@ -1286,13 +1289,13 @@ __global__ __launch_bounds__(kBigThreads, 4) void m1_big_scatter_kernel(
     }
     double bound;
     if (bound_in != nullptr) {
-      bound = bound_in[sl[t].pad];
+      bound = bound_in[sl[t].id];
     } else {
       const double bm = __longlong_as_double((long long)s_max[t < nt ? t : 0]);
       int e = 0;
       (void)frexp(bm, &e);  // 2^(e - 1) <= bm < 2^e
       bound = bm > 0.0 ? ldexp(1.0, e - 1) : 0.0;
-      if (t < nt && s == 0 && part == 0 && tid == 0) bound_out[sl[t].pad] = bound;
+      if (t < nt && s == 0 && part == 0 && tid == 0) bound_out[sl[t].id] = bound;
     }
     scale[t] = 0;
     if (bound > 0.0) {

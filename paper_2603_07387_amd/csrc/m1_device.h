@@ -1,6 +1,6 @@
-// Device code shared by the cyclic method's kernels (m1.hip, fused.hip):
-// element conversions, vector types, the packed mode hashes, the fixed-point
-// slot scatter and the LDS FFT.
+// Device code of the cyclic method's kernels: element conversions, vector types
+// and the LDS FFT (m1.hip, fused.hip), and the persistent kernel's fixed-point
+// slot scatter (fused.hip).
 #pragma once
 
 #include <type_traits>

@@ -10,10 +10,12 @@
 // not lead is first copied with them moved to the front), scatters every
 // virtual tensor once per sample, and combines, for each entry, the sketches
 // of the virtual tensors that entry selects (or, group by group, of those that
-// an assignment of the group's free modes selects: group_build).  Every entry uses the same count
-// sketches (the network's hash streams), so each tensor is read once per
-// sample pass however many entries it feeds: cost O(q N + n_out p m log m)
-// per sample, within the corollary's O(n^q' p m log m + q N).
+// an assignment of the group's free modes selects: group_build).  Every entry
+// uses the same count sketches (the network's hash streams), so each tensor is
+// read once per sample pass however many entries it feeds: cost O(q N + n_out p
+// m log m) per sample entry by entry, O(q N + T m log m + n_out m) in groups with
+// T transforms, T <= n_out p / 4; both within the corollary's O(n^q' p m log m +
+// q N).
 #include <algorithm>
 #include <cstring>
 #include <memory>

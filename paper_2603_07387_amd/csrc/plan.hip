@@ -117,7 +117,7 @@ int add_tensor_slots(tn_plan *p, int32_t gtensor, int32_t mode0, int q, const in
     sl.mode0 = mode0;
     sl.rows = (int32_t)std::min<int64_t>(rows_per, R - r0);
     sl.row0 = r0;
-    sl.pad = (int32_t)p->h_slots.size();
+    sl.id = (int32_t)p->h_slots.size();
     sl.magic = L > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint64_t)L + 1) : 0u;
     p->h_slots.push_back(sl);
   }
@@ -344,7 +344,7 @@ int m1_layout(tn_plan *p, const std::vector<NetCheck> *chkp) {
     std::vector<int32_t> pairs, pair0, place;
     if (p->big_scatter) {
       place.resize(sorted.size());
-      for (size_t i = 0; i < sorted.size(); ++i) place[(size_t)sorted[i].pad] = (int32_t)i;
+      for (size_t i = 0; i < sorted.size(); ++i) place[(size_t)sorted[i].id] = (int32_t)i;
     }
     auto name = [&](int32_t k) { return p->big_scatter ? place[(size_t)k] : k; };
     for (const NetDesc &nd : p->h_nets) {

@@ -67,7 +67,7 @@ struct ScatterSlot {
   int32_t rows;       // rows in this block
   int64_t row0;       // first row of the block
   uint32_t magic;     // ceil(2^32 / L): row = umulhi(e, magic) for e < 2^21
-  int32_t pad;        // the slot's number (in the plan's order of slots)
+  int32_t id;         // the slot's number (in the plan's order of slots)
 };
 
 // Per network: its tensors [t0, t1) and, per tensor, slots
